@@ -49,9 +49,9 @@ def _code_only(src: str) -> str:
 
 
 def kernel_source_hash(read=None):
-    """Hash of the code of the forward kernels (dfw_math.hpp, dfw_step.hip)."""
+    """Hash of the code of the forward kernels (dfw_math.hpp, dfw_math_f32.hpp, dfw_step.hip)."""
     h = hashlib.sha256()
-    for f in ("dfw_math.hpp", "dfw_step.hip"):
+    for f in ("dfw_math.hpp", "dfw_math_f32.hpp", "dfw_step.hip"):
         path = os.path.join(ROOT, "paper_2402_10914_amd", "csrc", f)
         if read:
             text = read(f)
@@ -366,7 +366,7 @@ def main():
         ms1, n1 = prof["faces1"]
         avg_s = ms1 / n1 / 1e3
         faces = (prob.nx + 1) * prob.ny + prob.nx * (prob.ny + 1)
-        fl = faces * flops.per_interface(prob.flux, 1)
+        fl = faces * flops.per_interface(prob.flux, 1, dt_name)
         achieved = fl / avg_s / 1e12
         peak = PEAK_FP64_VALU if esize == 8 else PEAK_FP32_VALU
         roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
@@ -400,7 +400,7 @@ def main():
         "roofline": roofline,
         "hbm_algorithmic": {"bytes_per_cell_update": BYTES_PER_CELL_UPDATE[esize], "achieved_GBps": round(hbm, 1),
                             "peak_GBps": PEAK_HBM, "frac": round(hbm / PEAK_HBM, 4)} if default_form else None,
-        "flops_per_cell_update": flops.per_cell_update(prob.flux) if default_form else None,
+        "flops_per_cell_update": flops.per_cell_update(prob.flux, dt_name) if default_form else None,
         "kernels": kernels,
         "cpu_baseline": None if args.no_cpu_baseline else cpu_baseline(prob, args.cpu_steps, args.cpu_cells, tl, ts),
         "batched": None if args.no_batch else batch_compare(),

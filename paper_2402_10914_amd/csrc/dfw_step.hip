@@ -28,6 +28,7 @@
 
 #include "../../include/dfweno.h"
 #include "dfw_math.hpp"
+#include "dfw_math_f32.hpp"
 
 namespace dfw {
 
@@ -316,6 +317,10 @@ __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict_
   real wln[4] = {0, 0, 0, 0}, wrn[4] = {0, 0, 0, 0};
   real om = real(1);  // time-limiter weight of this interface segment, from the normal sweep
   real* const omp = (OUT & OUT_OMEGA) ? &om : nullptr;
+  // the interface's basis, formed once: both sweeps of a thread work on the same two cells (the FP32
+  // form forms it in each)
+  Basis<real> B{};
+  constexpr bool kF32 = std::is_same<real, float>::value;
 
   // ---- normal sweep (Section 3.1): line values of both sides and their normal derivatives
   if (live1) {
@@ -325,12 +330,18 @@ __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict_
 #pragma unroll
       for (int c = 0; c < 4; ++c) cell[m][c] = sW[c][rr][fl + m];
     real wl[4], wr[4];
-    if (S.cw)  // uniform over the launch
-      normal_sweep<real, false>(cell, sA[rr][fl], sA[rr][fl + 1], sA[rr][fl + 2], sA[rr][fl + 3], inv_dn, k, wl, wr,
-                                wln, wrn, omp);
-    else
-      normal_sweep<real, true>(cell, sA[rr][fl], sA[rr][fl + 1], sA[rr][fl + 2], sA[rr][fl + 3], inv_dn, k, wl, wr,
-                               wln, wrn, omp);
+    const real a0 = sA[rr][fl], a1 = sA[rr][fl + 1], a2 = sA[rr][fl + 2], a3 = sA[rr][fl + 3];
+    if constexpr (kF32) {
+      if (S.cw)
+        cand::normal_sweep<false>(cell, a0, a1, a2, a3, inv_dn, k, wl, wr, wln, wrn, omp);
+      else
+        cand::normal_sweep<true>(cell, a0, a1, a2, a3, inv_dn, k, wl, wr, wln, wrn, omp);
+    } else if (S.cw) {  // uniform over the launch
+      normal_sweep_basis<false>(B, cell, a0, a1, a2, a3, inv_dn, k, wl, wr, wln, wrn, omp);
+    } else {
+      B = make_basis(cell[2], cell[3], k);
+      normal_sweep_basis<true>(B, cell, a0, a1, a2, a3, inv_dn, k, wl, wr, wln, wrn, omp);
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       sLine[c][tid] = wl[c];
@@ -342,12 +353,6 @@ __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict_
   // ---- tangential sweep at the Gauss points, fluxes, DF
   const bool live2 = f <= Nn && rr >= 2 && rr < TR + 2 && t < Nt;
   if (!live2) return;
-  real wa[4], wb[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    wa[c] = sW[c][rr][fl + 2];
-    wb[c] = sW[c][rr][fl + 3];
-  }
   real al[2][3];
 #pragma unroll
   for (int side = 0; side < 2; ++side)  // DF of the cell on the same side as the Gauss point
@@ -355,12 +360,26 @@ __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict_
     for (int q = 0; q < 3; ++q) al[side][q] = sA[rr - 1 + q][fl + 1 + side];
   auto line = [&](int side, int m, int c) -> real { return sLine[4 * side + c][tid + (m - 2) * rstride]; };
   real Fs[4], Fts[4], dfp;
-  if (S.cw)
-    segment_fluxes<real, FLUX, (OUT & OUT_F) != 0, (OUT & OUT_DF) != 0, false>(wa, wb, line, al, wln, wrn, dt, inv_dt,
-                                                                               k, Fs, Fts, dfp);
-  else
-    segment_fluxes<real, FLUX, (OUT & OUT_F) != 0, (OUT & OUT_DF) != 0, true>(wa, wb, line, al, wln, wrn, dt, inv_dt,
-                                                                              k, Fs, Fts, dfp);
+  constexpr bool kF = (OUT & OUT_F) != 0, kDF = (OUT & OUT_DF) != 0;
+  if constexpr (kF32) {
+    real wa[4], wb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      wa[c] = sW[c][rr][fl + 2];
+      wb[c] = sW[c][rr][fl + 3];
+    }
+    if (S.cw)
+      cand::segment_fluxes<FLUX, kF, kDF, false>(wa, wb, line, al, wln, wrn, dt, inv_dt, k, Fs, Fts, dfp);
+    else
+      cand::segment_fluxes<FLUX, kF, kDF, true>(wa, wb, line, al, wln, wrn, dt, inv_dt, k, Fs, Fts, dfp);
+  } else {
+    real gw[2][2][4], gwt[2][2][4];
+    if (S.cw)
+      segment_states<false>(B, line, al, inv_dt, k, gw, gwt);
+    else
+      segment_states<true>(B, line, al, inv_dt, k, gw, gwt);
+    segment_point_fluxes<FLUX, kF, kDF>(gw, gwt, wln, wrn, dt, k, Fs, Fts, dfp);
+  }
   // ---- write face sums (quadrature weights 1/2), components back to the global order
   const size_t fstride = dir == 0 ? (size_t)ny * (nx + 1) : (size_t)(ny + 1) * nx;
   real* Fo = dir == 0 ? FX + (size_t)t * (nx + 1) + f : FY + (size_t)f * nx + t;

@@ -34,17 +34,19 @@ def counts() -> dict:
         return json.load(f)
 
 
-def per_interface(flux: int, stage: int) -> int:
-    """Flops of one interface segment (normal sweep + tangential sweep + two Gauss-point fluxes)."""
+def per_interface(flux: int, stage: int, dtype: str = "f64") -> int:
+    """Flops of one interface segment (normal sweep + tangential sweep + two Gauss-point fluxes) in
+    the form the kernels of that element type run."""
     c = counts()
-    seg = c["segment_%s_stage%d" % ("gks" if flux == 1 else "lf", stage)]["flops"]
-    return c["normal_sweep"]["flops"] + seg
+    pre = "f32_" if dtype == "f32" else ""
+    seg = c["%ssegment_%s_stage%d" % (pre, "gks" if flux == 1 else "lf", stage)]["flops"]
+    return c[pre + "normal_sweep"]["flops"] + seg
 
 
-def per_cell_update(flux: int) -> int:
+def per_cell_update(flux: int, dtype: str = "f64") -> int:
     """Flops of one cell advanced by one S2O4 step (two interfaces per cell per stage)."""
     c = counts()
-    return 2 * (per_interface(flux, 1) + per_interface(flux, 2)) + c["update1_per_cell"] + c["update2_per_cell"]
+    return 2 * (per_interface(flux, 1, dtype) + per_interface(flux, 2, dtype)) + c["update1_per_cell"] + c["update2_per_cell"]
 
 
 if __name__ == "__main__":

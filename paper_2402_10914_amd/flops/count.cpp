@@ -12,6 +12,7 @@
 #include <cstdio>
 
 #include "../csrc/dfw_math.hpp"
+#include "../csrc/dfw_math_f32.hpp"
 
 namespace cnt {
 long long n_add = 0, n_mul = 0, n_div = 0, n_sqrt = 0, n_exp = 0, n_erfc = 0;
@@ -94,7 +95,8 @@ static void state(double x, C* w) {  // smooth sample state
 struct Count { long long total, div, sqrt_, exp_, erfc_; };
 static Count snap() { return Count{cnt::total(), cnt::n_div, cnt::n_sqrt, cnt::n_exp, cnt::n_erfc}; }
 
-template <int FLUX, bool F, bool DF>
+// FORM 0: the FP64 kernels' difference form, 1: the FP32 kernels' candidate form.
+template <int FORM, int FLUX, bool F, bool DF>
 static Count segment() {
   dfw::Coef<C> k = coef();
   C wa[4], wb[4], wln[4], wrn[4], lines[2][5][4];
@@ -104,25 +106,43 @@ static Count segment() {
   C al[2][3];
   for (int s = 0; s < 2; ++s) for (int q = 0; q < 3; ++q) al[s][q] = cnt::run(1.0);
   auto line = [&](int side, int m, int c) -> C { return lines[side][m][c]; };
-  C Fs[4], Fts[4], dfp;
+  C Fs[4], Fts[4], dfp, gw[2][2][4], gwt[2][2][4];
+  const dfw::Basis<C> B = dfw::make_basis(wa, wb, k);
   cnt::reset();
-  dfw::segment_fluxes<C, FLUX, F, DF>(wa, wb, line, al, wln, wrn, cnt::run(1e-3), cnt::run(100.0), k, Fs, Fts, dfp);
+  if (FORM == 0) {  // the basis is the one the normal sweep formed
+    dfw::segment_states<true>(B, line, al, cnt::run(100.0), k, gw, gwt);
+    dfw::segment_point_fluxes<FLUX, F, DF>(gw, gwt, wln, wrn, cnt::run(1e-3), k, Fs, Fts, dfp);
+  } else {
+    dfw::cand::segment_fluxes<FLUX, F, DF, true>(wa, wb, line, al, wln, wrn, cnt::run(1e-3), cnt::run(100.0), k, Fs, Fts,
+                                                 dfp);
+  }
   return snap();
 }
 
+template <int FORM>
 static Count normal() {
   dfw::Coef<C> k = coef();
   C cell[6][4], wl[4], wr[4], wln[4], wrn[4];
   for (int m = 0; m < 6; ++m) state(0.05 * m, cell[m]);
   cnt::reset();
   const C one = cnt::run(1.0);
-  dfw::normal_sweep<C>(cell, one, one, one, one, cnt::run(100.0), k, wl, wr, wln, wrn);
+  if (FORM == 0) dfw::normal_sweep<C>(cell, one, one, one, one, cnt::run(100.0), k, wl, wr, wln, wrn);
+  else dfw::cand::normal_sweep<true>(cell, one, one, one, one, cnt::run(100.0), k, wl, wr, wln, wrn);
   return snap();
 }
 
-static void print(const char* name, Count c, bool comma) {
-  std::printf("  \"%s\": {\"flops\": %lld, \"div\": %lld, \"sqrt\": %lld, \"exp\": %lld, \"erfc\": %lld}%s\n", name,
-              c.total, c.div, c.sqrt_, c.exp_, c.erfc_, comma ? "," : "");
+static void print(const char* prefix, const char* name, Count c) {
+  std::printf("  \"%s%s\": {\"flops\": %lld, \"div\": %lld, \"sqrt\": %lld, \"exp\": %lld, \"erfc\": %lld},\n", prefix,
+              name, c.total, c.div, c.sqrt_, c.exp_, c.erfc_);
+}
+
+template <int FORM>
+static void counts(const char* prefix) {
+  print(prefix, "normal_sweep", normal<FORM>());
+  print(prefix, "segment_lf_stage1", segment<FORM, 0, true, false>());
+  print(prefix, "segment_lf_stage2", segment<FORM, 0, false, true>());
+  print(prefix, "segment_gks_stage1", segment<FORM, 1, true, false>());
+  print(prefix, "segment_gks_stage2", segment<FORM, 1, false, true>());
 }
 
 int main() {
@@ -130,11 +150,8 @@ int main() {
   // 8 add) and W*, R (3 coefficient products, 16 mul, 16 add); update 2 forms dL/dt (20), the new
   // state (1 + 8), the DF product (3) and the signal speed (1 div, 8 mul/add, 1 sqrt, 2 mul).
   std::printf("{\n");
-  print("normal_sweep", normal(), true);
-  print("segment_lf_stage1", segment<0, true, false>(), true);
-  print("segment_lf_stage2", segment<0, false, true>(), true);
-  print("segment_gks_stage1", segment<1, true, false>(), true);
-  print("segment_gks_stage2", segment<1, false, true>(), true);
+  counts<0>("");
+  counts<1>("f32_");
   std::printf("  \"update1_per_cell\": 75,\n  \"update2_per_cell\": 45\n}\n");
   return 0;
 }
