@@ -37,12 +37,12 @@ DFW_HD void make_basis_adj(const real* wa, const real* wb, const Coef<real>& k, 
   real c2 = k.gamma * p * ir;
   real c = sqrt(c2);
   real ic = real(1) / c;
-  real b1 = k.gm1 / c2;
+  real b1 = real(0.5) * k.gm1 / c2;
   real l_hq2 = lB.hq2 + lB.b2 * b1;
   real l_b1 = lB.b1 + lB.b2 * hq2;
   real l_c2 = -l_b1 * b1 / c2;
   real l_e = lB.H * ir, l_p = lB.H * ir, l_ir = lB.H * (e + p);
-  real l_c = lB.c - lB.ic * ic * ic;
+  real l_c = lB.c - real(0.5) * lB.ic * ic * ic;
   l_c2 += l_c * real(0.5) / c;
   l_p += l_c2 * k.gamma * ir;
   l_ir += l_c2 * k.gamma * p;
@@ -63,9 +63,8 @@ DFW_HD void make_basis_adj(const real* wa, const real* wb, const Coef<real>& k, 
 
 template <class real>
 DFW_HD void project_adj(const Basis<real>& B, const real* w, const real* lq, real* lw, BasisAdj<real>& lB) {
-  const real h = real(0.5);
-  real lT = h * lq[0] - lq[1] + h * lq[3];
-  real ls = h * lq[0] - h * lq[3];
+  real lT = lq[0] - real(2) * lq[1] + lq[3];
+  real ls = lq[0] - lq[3];
   lw[0] += lq[1] - B.v * lq[2];
   lw[2] += lq[2];
   lB.v += -w[0] * lq[2];
@@ -132,9 +131,9 @@ template <int C, class real>
 DFW_HD real project_comp(const Basis<real>& B, const real* w) {
   if (C == 2) return w[2] - B.v * w[0];
   const real T = B.b2 * w[0] - B.b1 * (B.u * w[1] + B.v * w[2] - w[3]);
-  if (C == 1) return w[0] - T;
+  if (C == 1) return w[0] - real(2) * T;
   const real s = (B.u * w[0] - w[1]) * B.ic;
-  return C == 0 ? real(0.5) * (T + s) : real(0.5) * (T - s);
+  return C == 0 ? T + s : T - s;
 }
 
 template <int C, class real>
@@ -148,10 +147,10 @@ DFW_HD void project_adj_comp(const Basis<real>& B, const real* w, real lqc, real
   real lT, ls = real(0);
   if (C == 1) {
     lw[0] += lqc;
-    lT = -lqc;
+    lT = real(-2) * lqc;
   } else {
-    lT = real(0.5) * lqc;
-    ls = C == 0 ? real(0.5) * lqc : real(-0.5) * lqc;
+    lT = lqc;
+    ls = C == 0 ? lqc : -lqc;
   }
   if (C != 1) {
     lB.u += ls * w[0] * B.ic;

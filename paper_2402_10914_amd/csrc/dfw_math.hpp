@@ -46,6 +46,49 @@ DFW_HD real rcp_pos(real x) {
   return real(1) / x;
 }
 
+// Reciprocal with IEEE results for zero, infinite and NaN operands (densities, pressures and sums of
+// them on failing states, where inf and not NaN has to reach the steps that rely on it): the refined
+// estimate of rcp_pos, special cases set by the division fix-up instruction; 5 instructions.
+DFW_HD double rcp_any(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_div_fixup(rcp_pos(x), x, 1.0);
+#else
+  return 1.0 / x;
+#endif
+}
+
+template <class real>
+DFW_HD real rcp_any(real x) {
+  return real(1) / x;
+}
+
+// s = sqrt(x) and is = 1 / s together, with IEEE results at zero, infinity, NaN and negative x: the
+// hardware estimate y of 1/sqrt(x) refined by one cubic step (e = 1 - x y^2, y + y e (1/2 + 3/8 e)),
+// the root corrected by its residual; 14 instructions instead of about 30 for the library's square
+// root and an IEEE division.  Zero and +inf are their own roots; a negative x leaves NaN (the
+// division fix-up takes a NaN quotient for an overflow, so it serves the reciprocal only, where the
+// NaN is the divisor).
+DFW_HD void sqrt_inv(double x, double& s, double& is) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  y = fma(y * e, fma(e, 0.375, 0.5), y);
+  const double r = x * y;
+  constexpr int kZeroOrInf = 1 << 5 | 1 << 6 | 1 << 9;  // class bits: -0, +0, +inf
+  s = __builtin_amdgcn_class(x, kZeroOrInf) ? x : fma(fma(-r, r, x), 0.5 * y, r);
+  is = __builtin_amdgcn_div_fixup(y, s, 1.0);
+#else
+  s = sqrt(x);
+  is = 1.0 / s;
+#endif
+}
+
+template <class real>
+DFW_HD void sqrt_inv(real x, real& s, real& is) {
+  s = sqrt(x);
+  is = real(1) / s;
+}
+
 // a b + c in one rounding (the counting scalar of the flop counts: a multiply and an add).
 DFW_HD double fmadd(double a, double b, double c) { return fma(a, b, c); }
 DFW_HD float fmadd(float a, float b, float c) { return fmaf(a, b, c); }
@@ -84,9 +127,9 @@ DFW_HD bool df_switch(real a_lo, real a_c, real a_hi, const Coef<real>& k) {
 // ------------------------------------------------------------------------------------------------
 // Characteristic basis (eigenvectors of the normal flux Jacobian at the arithmetic mean of the two
 // cells beside the interface).  Right eigenvectors (columns): (1,u-c,v,H-uc), (1,u,v,q2/2),
-// (0,0,1,v), (1,u+c,v,H+uc).  The left eigenvectors are applied in a factored closed form:
-// with b1 = (gamma-1)/c^2, b2 = b1 q2/2 and T = b2 w0 - b1 (u w1 + v w2 - w3), s = (u w0 - w1)/c:
-//   Q0 = (T + s)/2, Q1 = w0 - T, Q2 = w2 - v w0, Q3 = (T - s)/2.
+// (0,0,1,v), (1,u+c,v,H+uc).  The left eigenvectors are applied in a factored closed form: with
+// b1 = (gamma-1)/(2 c^2), b2 = b1 q2/2, ic = 1/(2 c) and T = b2 w0 - b1 (u w1 + v w2 - w3),
+// s = (u w0 - w1) ic:  Q0 = T + s, Q1 = w0 - 2 T, Q2 = w2 - v w0, Q3 = T - s.
 // ------------------------------------------------------------------------------------------------
 template <class real>
 struct Basis {
@@ -101,16 +144,16 @@ DFW_HD Basis<real> make_basis(const real* wa, const real* wb, const Coef<real>& 
   real m = h * (wa[1] + wb[1]);
   real n = h * (wa[2] + wb[2]);
   real e = h * (wa[3] + wb[3]);
-  real ir = real(1) / r;
+  real ir = rcp_any(r);
   B.u = m * ir;
   B.v = n * ir;
   B.hq2 = h * (B.u * B.u + B.v * B.v);
   real p = k.gm1 * (e - r * B.hq2);
-  real c2 = k.gamma * p * ir;
-  B.c = sqrt(c2);
-  B.ic = real(1) / B.c;
+  real ic;
+  sqrt_inv(k.gamma * p * ir, B.c, ic);
+  B.ic = h * ic;
   B.H = (e + p) * ir;
-  B.b1 = k.gm1 * (B.ic * B.ic);  // (gamma - 1) / c^2 from the reciprocal already formed
+  B.b1 = k.gm1 * (B.ic * ic);
   B.b2 = B.hq2 * B.b1;
   return B;
 }
@@ -119,10 +162,10 @@ template <class real>
 DFW_HD void project(const Basis<real>& B, const real* w, real* q) {
   real T = B.b2 * w[0] - B.b1 * (B.u * w[1] + B.v * w[2] - w[3]);
   real s = (B.u * w[0] - w[1]) * B.ic;
-  q[0] = real(0.5) * (T + s);
-  q[1] = w[0] - T;
+  q[0] = T + s;
+  q[1] = w[0] - real(2) * T;
   q[2] = w[2] - B.v * w[0];
-  q[3] = real(0.5) * (T - s);
+  q[3] = T - s;
 }
 
 template <class real>
@@ -418,29 +461,38 @@ DFW_HD void recon_poly(const real* Q, real a_lo, real a_c, real a_hi, const Coef
 // ------------------------------------------------------------------------------------------------
 template <class real>
 struct Prim {
-  real r, ir, u, v, p, c;
+  real r, ir, u, v, p, c, ic;  // ir = 1/r, ic = 1/c
 };
 
 template <class real>
 DFW_HD Prim<real> prim(const real* w, const Coef<real>& k) {
   Prim<real> q;
   q.r = w[0];
-  q.ir = real(1) / w[0];
+  q.ir = rcp_any(w[0]);
   q.u = w[1] * q.ir;
   q.v = w[2] * q.ir;
   q.p = k.gm1 * (w[3] - real(0.5) * (w[1] * q.u + w[2] * q.v));
-  q.c = sqrt(k.gamma * q.p * q.ir);
+  sqrt_inv(k.gamma * q.p * q.ir, q.c, q.ic);
   return q;
+}
+
+// 1/p as gamma/(rho c^2), from the reciprocals already formed.
+template <class real>
+DFW_HD real df_factor(const Prim<real>& L, const Prim<real>& R, const Coef<real>& k) {
+  const real jump = fabs(L.p - R.p);
+  const real dn = L.u * L.ic - R.u * R.ic;
+  const real dt = L.v * L.ic - R.v * R.ic;
+  const real D = k.gamma * jump * (L.ir * (L.ic * L.ic) + R.ir * (R.ic * R.ic)) + dn * dn + dt * dt;
+  return rcp_any(real(1) + D * D);
 }
 
 template <class real>
 DFW_HD real df_factor(const Prim<real>& L, const Prim<real>& R) {
   real jump = fabs(L.p - R.p);
-  real icl = real(1) / L.c, icr = real(1) / R.c;
-  real dn = L.u * icl - R.u * icr;
-  real dt = L.v * icl - R.v * icr;
-  real D = jump * (real(1) / L.p + real(1) / R.p) + dn * dn + dt * dt;
-  return real(1) / (real(1) + D * D);
+  real dn = L.u * L.ic - R.u * R.ic;
+  real dt = L.v * L.ic - R.v * R.ic;
+  real D = jump * (rcp_any(L.p) + rcp_any(R.p)) + dn * dn + dt * dt;
+  return rcp_any(real(1) + D * D);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -450,26 +502,28 @@ DFW_HD real df_factor(const Prim<real>& L, const Prim<real>& R) {
 //   v_t = -(u v_x + v v_y + p_y/rho),  p_t = -(u p_x + v p_y + gamma p (u_x + v_y)),
 // and dF/dt = (F_t^l + F_t^r)/2 - s (W_t^r - W_t^l)/2 with the LF speed s held fixed.
 // ------------------------------------------------------------------------------------------------
+// In the products of the density with the derivatives (a = rho u_x, ..., in the order u_x, u_y, v_x,
+// v_y), which need no reciprocal: rho_t = -((rho u)_x + (rho v)_y), Au = -rho u_t, Av = -rho v_t.
 template <class real>
 DFW_HD void euler_time_derivs(const real* w, const Prim<real>& q, const real* wx, const real* wy,
                               const Coef<real>& k, real* wt, real* ft) {
-  real ke = real(0.5) * (q.u * q.u + q.v * q.v);
-  real ux = (wx[1] - q.u * wx[0]) * q.ir, vx = (wx[2] - q.v * wx[0]) * q.ir;
-  real px = k.gm1 * (wx[3] - q.u * wx[1] - q.v * wx[2] + ke * wx[0]);
-  real uy = (wy[1] - q.u * wy[0]) * q.ir, vy = (wy[2] - q.v * wy[0]) * q.ir;
-  real py = k.gm1 * (wy[3] - q.u * wy[1] - q.v * wy[2] + ke * wy[0]);
-  real rt = -(q.u * wx[0] + q.r * ux + q.v * wy[0] + q.r * vy);
-  real ut = -(q.u * ux + q.v * uy + px * q.ir);
-  real vt = -(q.u * vx + q.v * vy + py * q.ir);
-  real pt = -(q.u * px + q.v * py + k.gamma * q.p * (ux + vy));
+  const real ke = real(0.5) * (q.u * q.u + q.v * q.v);
+  const real ux = wx[1] - q.u * wx[0], vx = wx[2] - q.v * wx[0];
+  const real uy = wy[1] - q.u * wy[0], vy = wy[2] - q.v * wy[0];
+  const real px = k.gm1 * (wx[3] - q.u * wx[1] - q.v * wx[2] + ke * wx[0]);
+  const real py = k.gm1 * (wy[3] - q.u * wy[1] - q.v * wy[2] + ke * wy[0]);
+  const real rt = -(wx[1] + wy[2]);
+  const real Au = fmadd(q.u, ux, fmadd(q.v, uy, px));
+  const real Av = fmadd(q.u, vx, fmadd(q.v, vy, py));
+  const real pt = -fmadd(q.u, px, fmadd(q.v, py, (k.gamma * q.p * q.ir) * (ux + vy)));
   wt[0] = rt;
-  wt[1] = rt * q.u + q.r * ut;
-  wt[2] = rt * q.v + q.r * vt;
-  wt[3] = pt * k.inv_gm1 + rt * ke + q.r * (q.u * ut + q.v * vt);
+  wt[1] = fmadd(rt, q.u, -Au);
+  wt[2] = fmadd(rt, q.v, -Av);
+  wt[3] = fmadd(pt, k.inv_gm1, fmadd(rt, ke, -fmadd(q.u, Au, q.v * Av)));
   ft[0] = wt[1];
-  ft[1] = wt[1] * q.u + w[1] * ut + pt;
-  ft[2] = wt[1] * q.v + w[1] * vt;
-  ft[3] = ut * (w[3] + q.p) + q.u * (wt[3] + pt);
+  ft[1] = fmadd(q.u, wt[1] - Au, pt);
+  ft[2] = fmadd(wt[1], q.v, -(q.u * Av));
+  ft[3] = fmadd(q.u, wt[3] + pt, -(((w[3] + q.p) * q.ir) * Au));
 }
 
 template <class real, bool WANT_F>
@@ -615,104 +669,192 @@ DFW_HD void micro_slope(const real* g, real U, real V, real lam, real h, const C
   s[0] = g[0] - U * s[1] - V * s[2] - real(0.5) * s[3] * B;
 }
 
+// The slopes of a Maxwellian enter the flux only through moments <(s . psi) u^a v^b psi>, and since
+// rho (s . psi) g is the derivative of rho g in that direction, such a moment is the derivative of
+// rho <u^a v^b psi>, a product of u-moments mu_n(U, h) with polynomials in V and h = p/rho.  So no slope s is formed: with the derivative's density r = rho_x, a = rho U_x,
+// b = rho V_x and e = rho h_x, and d mu_n/dU = n mu_{n-1}, d mu_n/dh = n (n-1)/2 mu_{n-2},
+//   D_n = (rho mu_n)_x = r mu_n + n a mu_{n-1} + n (n-1)/2 e mu_{n-2}
+// in full space and, for n >= 2, in a half space too; there mu_0 and mu_1 have the boundary terms
+//   D_0 = r mu_0 + G (a - U e/(2h)),  D_1 = r mu_1 + a mu_0 + G e/2,  G = +-exp(-U^2/(2h)) / sqrt(2 pi h).
+// This took the flux of one Gauss point from about 1 200 instructions (slopes from the inverse moment
+// matrix, moments up to order 6 folded per slope) to about 600, most of the rest being the exponential,
+// error function and root of the two half spaces.
+template <class real>
+struct GasSlope {
+  real r, a, b, e;
+};
+
+template <class real>
+DFW_HD GasSlope<real> gas_slope(const real* w, real U, real V, real h, real ke, const Coef<real>& k) {
+  GasSlope<real> s;
+  s.r = w[0];
+  s.a = w[1] - U * w[0];
+  s.b = w[2] - V * w[0];
+  s.e = fmadd(-h, w[0], k.gm1 * (w[3] - U * w[1] - V * w[2] + ke * w[0]));
+  return s;
+}
+
+// D_n for n = 1 (full space) and n = 2, 3, 4 from the u-moments mu[0..4].
+template <class real>
+DFW_HD real slope_d1(const GasSlope<real>& s, const real* mu) { return fmadd(s.r, mu[1], s.a * mu[0]); }
+template <class real>
+DFW_HD real slope_d2(const GasSlope<real>& s, const real* mu) {
+  return fmadd(s.r, mu[2], fmadd(real(2) * s.a, mu[1], s.e * mu[0]));
+}
+template <class real>
+DFW_HD real slope_d3(const GasSlope<real>& s, const real* mu) {
+  return fmadd(s.r, mu[3], real(3) * fmadd(s.a, mu[2], s.e * mu[1]));
+}
+template <class real>
+DFW_HD real slope_d4(const GasSlope<real>& s, const real* mu) {
+  return fmadd(s.r, mu[4], fmadd(real(4) * s.a, mu[3], (real(6) * s.e) * mu[2]));
+}
+
+// M += (rho <u^2 psi>)_x + (rho <u v psi>)_y for the slopes sx, sy of one Maxwellian (mean V, X = <v^2 +
+// xi^2>, d1 = D_1 of sy); the energy component is left doubled.
+template <class real>
+DFW_HD void add_second_moments(const GasSlope<real>& sx, const GasSlope<real>& sy, const real* mu, real V, real h,
+                               real X, real d1, const Coef<real>& k, real* M) {
+  const real K1 = k.K + real(1), K3 = k.K + real(3);
+  const real d2 = slope_d2(sx, mu), d3 = slope_d3(sx, mu), d4 = slope_d4(sx, mu);
+  M[0] += d2;
+  M[1] += d3;
+  M[2] += fmadd(V, d2, sx.b * mu[2]);
+  M[3] += fmadd(X, d2, fmadd(mu[2], fmadd(real(2) * V, sx.b, K1 * sx.e), d4));
+  const real t2 = slope_d2(sy, mu), t3 = slope_d3(sy, mu);
+  const real vb = real(2) * V * sy.b, Z = fmadd(real(2), h, X);  // Z = <v^3 + v xi^2> / V
+  M[0] += fmadd(V, d1, mu[1] * sy.b);
+  M[1] += fmadd(V, t2, mu[2] * sy.b);
+  M[2] += fmadd(fmadd(V, V, h), d1, mu[1] * (vb + sy.e));
+  M[3] += fmadd(V, fmadd(Z, d1, fmadd(mu[1], fmadd(K3, sy.e, vb), t3)), sy.b * fmadd(Z, mu[1], mu[3]));
+}
+
+// Half-space part of one side (SG = +1: left state, u > 0; -1: right state, u < 0) added to the sums; energy
+// components doubled.  s2h = sqrt(2 h) and its reciprocal is.
+template <int SG, class real>
+DFW_HD void gks_side(const Prim<real>& q, real h, real s2h, real is, const real* wn, const real* wt,
+                     const Coef<real>& k, real* Wc, real* Wcn, real* Wct, real* Flr, real* Malr) {
+  const real inv_sqrt_pi = real(SG * 0.56418958354775628695);
+  const real U = q.u, V = q.v, K1 = k.K + real(1);
+  const real z = is * U, ex = exp(-(z * z));
+  real mu[5];
+  mu[0] = real(0.5) * erfc(SG > 0 ? -z : z);
+  mu[1] = fmadd(U, mu[0], (real(0.5) * inv_sqrt_pi) * s2h * ex);
+  mu[2] = fmadd(U, mu[1], h * mu[0]);
+  mu[3] = fmadd(U, mu[2], real(2) * h * mu[1]);
+  mu[4] = fmadd(U, mu[3], real(3) * h * mu[2]);
+  const real G = inv_sqrt_pi * is * ex;
+  const real ke = real(0.5) * (U * U + V * V), X = fmadd(V, V, K1 * h);
+  const GasSlope<real> sx = gas_slope(wn, U, V, h, ke, k), sy = gas_slope(wt, U, V, h, ke, k);
+  const real zi = z * is;  // U / (2 h)
+  {
+    const real d0 = fmadd(sx.r, mu[0], G * fmadd(-zi, sx.e, sx.a));
+    Wcn[0] += d0;
+    Wcn[1] += fmadd(real(0.5) * G, sx.e, slope_d1(sx, mu));
+    Wcn[2] += fmadd(V, d0, sx.b * mu[0]);
+    Wcn[3] += fmadd(X, d0, fmadd(mu[0], fmadd(real(2) * V, sx.b, K1 * sx.e), slope_d2(sx, mu)));
+  }
+  const real t0 = fmadd(sy.r, mu[0], G * fmadd(-zi, sy.e, sy.a));
+  const real t1 = fmadd(real(0.5) * G, sy.e, slope_d1(sy, mu));
+  Wct[0] += t0;
+  Wct[1] += t1;
+  Wct[2] += fmadd(V, t0, sy.b * mu[0]);
+  Wct[3] += fmadd(X, t0, fmadd(mu[0], fmadd(real(2) * V, sy.b, K1 * sy.e), slope_d2(sy, mu)));
+  add_second_moments(sx, sy, mu, V, h, X, t1, k, Malr);
+  const real m0 = q.r * mu[0], m1 = q.r * mu[1], m2 = q.r * mu[2];
+  Wc[0] += m0;
+  Wc[1] += m1;
+  Wc[2] = fmadd(V, m0, Wc[2]);
+  Wc[3] += fmadd(X, m0, m2);
+  Flr[0] += m1;
+  Flr[1] += m2;
+  Flr[2] = fmadd(V, m1, Flr[2]);
+  Flr[3] += fmadd(X, m1, q.r * mu[3]);
+}
+
 // GKS flux at one Gauss point.  wl/wr: states; wln/wrn: normal derivatives; wlt/wrt: tangential
 // derivatives.  Outputs F (if WANT_F) and dF/dt by the S2O4 fit of eqs. (23)-(25) to the time
 // integrals over dt and dt/2, written in closed form:
 //   F    = cf1 Fc + cf2 (Ma_c - Ma_lr) + (1 - cf1) F_lr
 //   F_t  = ct1 (Fc - F_lr) + ct2 (Ma_c - Ma_lr) + MA_c
-// with E1 = exp(-dt/tau), E2 = exp(-dt/(2 tau)):
-//   cf1 = 1 - (tau/dt)(3 - 4E2 + E1),  cf2 = (tau^2/dt)(3 - 4E2 + E1) + tau (E1 - 2E2),
-//   ct1 = 4 tau (1 - E2)^2 / dt^2,     ct2 = 4 (tau dt E2 (1 - E2) - tau^2 (1 - E2)^2) / dt^2.
+// with x = tau/dt, E2 = exp(-1/(2 x)), E1 = E2^2, z = (1 - E2) (3 - E2):
+//   cf1 = 1 - x z,  cf2 = dt (x^2 z + x E2 (E2 - 2)),
+//   ct1 = 4 x (1 - E2)^2 / dt,  ct2 = 4 (x E2 (1 - E2) - x^2 (1 - E2)^2).
+// Fc and MA_c (the time derivative of the flux from the compatibility condition) are the Euler flux
+// of the equilibrium state and its Cauchy-Kovalevskaya derivative.  isl: 1/sqrt(2 h) of the two sides.
+template <bool WANT_F, class real>
+DFW_HD void gks_point_flux(const real* wln, const real* wlt, const real* wrn, const real* wrt, const Prim<real>& ql,
+                           const Prim<real>& qr, real dt, const Coef<real>& k, real* F, real* Ft, real* isl) {
+  real Wc[4] = {0, 0, 0, 0}, Wcn[4] = {0, 0, 0, 0}, Wct[4] = {0, 0, 0, 0};
+  real Flr[4] = {0, 0, 0, 0}, Malr[4] = {0, 0, 0, 0};
+  real s2h;
+  real h = ql.p * ql.ir;
+  sqrt_inv(real(2) * h, s2h, isl[0]);
+  gks_side<1>(ql, h, s2h, isl[0], wln, wlt, k, Wc, Wcn, Wct, Flr, Malr);
+  h = qr.p * qr.ir;
+  sqrt_inv(real(2) * h, s2h, isl[1]);
+  gks_side<-1>(qr, h, s2h, isl[1], wrn, wrt, k, Wc, Wcn, Wct, Flr, Malr);
+  Wc[3] *= real(0.5);
+  Wcn[3] *= real(0.5);
+  Wct[3] *= real(0.5);
+  // equilibrium state at the interface
+  Prim<real> c;
+  c.r = Wc[0];
+  c.ir = rcp_any(Wc[0]);
+  c.u = Wc[1] * c.ir;
+  c.v = Wc[2] * c.ir;
+  c.p = k.gm1 * (Wc[3] - real(0.5) * (Wc[1] * c.u + Wc[2] * c.v));
+  h = c.p * c.ir;
+  real Mac[4] = {0, 0, 0, 0}, MAc[4], wt[4];
+  {
+    const real U = c.u, V = c.v, K1 = k.K + real(1);
+    real mu[5];
+    mu[0] = real(1);
+    mu[1] = U;
+    mu[2] = fmadd(U, U, h);
+    mu[3] = fmadd(U, mu[2], real(2) * h * U);
+    mu[4] = fmadd(U, mu[3], real(3) * h * mu[2]);
+    const real ke = real(0.5) * (U * U + V * V);
+    const GasSlope<real> sx = gas_slope(Wcn, U, V, h, ke, k), sy = gas_slope(Wct, U, V, h, ke, k);
+    add_second_moments(sx, sy, mu, V, h, fmadd(V, V, K1 * h), slope_d1(sy, mu), k, Mac);
+  }
+  euler_time_derivs(Wc, c, Wcn, Wct, k, wt, MAc);
+  const real Fc[4] = {Wc[1], fmadd(Wc[1], c.u, c.p), Wc[2] * c.u, c.u * (Wc[3] + c.p)};
+  // time coefficients
+  const real x = k.c1 + k.c2 * fabs((ql.p - qr.p) * rcp_any(ql.p + qr.p));
+  const real E2 = exp(real(-0.5) * rcp_any(x));
+  const real om = real(1) - E2, xo = x * om;
+  const real ct1 = (real(4) * xo * om) * rcp_any(dt), ct2 = real(4) * xo * (E2 - xo);
+  const real z = om * (real(3) - E2);
+  const real cf1 = real(1) - x * z, cf2 = dt * (x * fmadd(x, z, E2 * (E2 - real(2))));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const real half = i == 3 ? real(0.5) : real(1);
+    const real dM = half * (Mac[i] - Malr[i]), flr = half * Flr[i], dF = Fc[i] - flr;
+    Ft[i] = fmadd(ct1, dF, fmadd(ct2, dM, MAc[i]));
+    if (WANT_F) F[i] = fmadd(cf1, dF, fmadd(cf2, dM, flr));
+  }
+}
+
 template <class real, bool WANT_F>
 DFW_HD void gks_flux(const real* wl, const real* wln, const real* wlt, const real* wr, const real* wrn,
                      const real* wrt, const Prim<real>& ql, const Prim<real>& qr, real dt,
                      const Coef<real>& k, real* F, real* Ft) {
-  real Wc[4] = {0, 0, 0, 0}, Wcn[4] = {0, 0, 0, 0}, Wct[4] = {0, 0, 0, 0};
-  real Flr[4] = {0, 0, 0, 0}, Malr[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const real* w = side == 0 ? wl : wr;
-    const real* wn = side == 0 ? wln : wrn;
-    const real* wt = side == 0 ? wlt : wrt;
-    const Prim<real>& q = side == 0 ? ql : qr;
-    real lam = real(0.5) * q.r / q.p;
-    Mom<real> M;
-    maxwell_moments(q.u, q.v, lam, q.p * q.ir, side == 0 ? 1 : -1, k, M);
-    real g[4], a[4], b[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) g[c] = wn[c] * q.ir;
-    micro_slope(g, q.u, q.v, lam, M.h, k, a);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) g[c] = wt[c] * q.ir;
-    micro_slope(g, q.u, q.v, lam, M.h, k, b);
-    real t0[4], t1[4], t2[4];
-    mom_psi(M, 0, 0, t0);
-    mom_s_psi(M, a, 0, 0, t1);
-    mom_s_psi(M, b, 0, 0, t2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      Wc[c] += q.r * t0[c];
-      Wcn[c] += q.r * t1[c];
-      Wct[c] += q.r * t2[c];
-    }
-    mom_psi(M, 1, 0, t0);
-    mom_s_psi(M, a, 2, 0, t1);
-    mom_s_psi(M, b, 1, 1, t2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      Flr[c] += q.r * t0[c];
-      Malr[c] += q.r * (t1[c] + t2[c]);
-    }
-  }
-  // equilibrium state at the interface
-  real irc = real(1) / Wc[0];
-  real Uc = Wc[1] * irc, Vc = Wc[2] * irc;
-  real pc = k.gm1 * (Wc[3] - real(0.5) * (Wc[1] * Uc + Wc[2] * Vc));
-  real lamc = real(0.5) * Wc[0] / pc;
-  Mom<real> M;
-  maxwell_moments(Uc, Vc, lamc, pc * irc, 0, k, M);
-  real g[4], ac[4], bc[4], Ac[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) g[c] = Wcn[c] * irc;
-  micro_slope(g, Uc, Vc, lamc, M.h, k, ac);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) g[c] = Wct[c] * irc;
-  micro_slope(g, Uc, Vc, lamc, M.h, k, bc);
-  // compatibility: <(A . psi) psi> = -<((a . psi) u + (b . psi) v) psi>
-  real t1[4], t2[4];
-  mom_s_psi(M, ac, 1, 0, t1);
-  mom_s_psi(M, bc, 0, 1, t2);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) g[c] = -(t1[c] + t2[c]);
-  micro_slope(g, Uc, Vc, lamc, M.h, k, Ac);
-  real Fc[4], Mac[4], MAc[4];
-  mom_psi(M, 1, 0, Fc);
-  mom_s_psi(M, ac, 2, 0, t1);
-  mom_s_psi(M, bc, 1, 1, t2);
-  mom_s_psi(M, Ac, 1, 0, MAc);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    Fc[c] *= Wc[0];
-    Mac[c] = Wc[0] * (t1[c] + t2[c]);
-    MAc[c] *= Wc[0];
-  }
-  // time coefficients
-  real tau = k.c1 * dt + k.c2 * fabs((ql.p - qr.p) / (ql.p + qr.p)) * dt;
-  real E2 = exp(-real(0.5) * dt / tau);
-  real E1 = E2 * E2;
-  real om = real(1) - E2;
-  real idt = real(1) / dt;
-  real ct1 = real(4) * tau * om * om * idt * idt;
-  real ct2 = real(4) * (tau * dt * E2 * om - tau * tau * om * om) * idt * idt;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) Ft[c] = ct1 * (Fc[c] - Flr[c]) + ct2 * (Mac[c] - Malr[c]) + MAc[c];
-  if (WANT_F) {
-    real z = real(3) - real(4) * E2 + E1;
-    real cf1 = real(1) - tau * idt * z;
-    real cf2 = tau * tau * idt * z + tau * (E1 - real(2) * E2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) F[c] = cf1 * Fc[c] + cf2 * (Mac[c] - Malr[c]) + (real(1) - cf1) * Flr[c];
-  }
+  (void)wl;
+  (void)wr;
+  real isl[2];
+  gks_point_flux<WANT_F>(wln, wlt, wrn, wrt, ql, qr, dt, k, F, Ft, isl);
+}
+
+// The DF of a Gauss point from isl = 1/sqrt(2 h) of its two sides, which the gas-kinetic flux has:
+// 1/p = 2 isl^2/rho, 1/c = isl sqrt(2/gamma); gamma D is formed, and 1/(1 + D^2) = gamma^2/(gamma^2 + (gamma D)^2).
+template <class real>
+DFW_HD real df_factor_gks(const Prim<real>& L, const Prim<real>& R, const real* isl, const Coef<real>& k) {
+  const real dn = L.u * isl[0] - R.u * isl[1], dt = L.v * isl[0] - R.v * isl[1];
+  const real jp = fabs(L.p - R.p) * (L.ir * (isl[0] * isl[0]) + R.ir * (isl[1] * isl[1]));
+  const real D = real(2) * fmadd(k.gamma, jp, fmadd(dn, dn, dt * dt));
+  const real g2 = k.gamma * k.gamma;
+  return g2 * rcp_any(fmadd(D, D, g2));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -834,16 +976,21 @@ DFW_HD void segment_point_fluxes(const real (*gw)[2][4], const real (*gwt)[2][4]
   for (int g = 0; g < 2; ++g) {
     Prim<real> ql = prim(gw[0][g], k), qr = prim(gw[1][g], k);
     real F[4], Ft[4];
-    if (FLUX == 0)
+    real df;
+    if (FLUX == 0) {
       lf_flux<real, WANT_F>(gw[0][g], wln, gwt[0][g], gw[1][g], wrn, gwt[1][g], ql, qr, k, F, Ft);
-    else
-      gks_flux<real, WANT_F>(gw[0][g], wln, gwt[0][g], gw[1][g], wrn, gwt[1][g], ql, qr, dt, k, F, Ft);
+      if (WANT_DF) df = df_factor(ql, qr, k);
+    } else {
+      real isl[2];
+      gks_point_flux<WANT_F>(wln, gwt[0][g], wrn, gwt[1][g], ql, qr, dt, k, F, Ft, isl);
+      if (WANT_DF) df = df_factor_gks(ql, qr, isl, k);
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (WANT_F) Fs[c] += F[c];
       Fts[c] += Ft[c];
     }
-    if (WANT_DF) dfp *= df_factor(ql, qr);
+    if (WANT_DF) dfp *= df;
   }
 }
 

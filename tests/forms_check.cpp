@@ -1,8 +1,9 @@
-// Host check of the difference form of the reconstruction (dfw_math.hpp, the FP64 kernels) against
+// Host check of the forms of dfw_math.hpp (the FP64 kernels) against
 // the candidate form (dfw_math_f32.hpp, here in FP64 too) through the functions that the interface
 // kernel calls: the normal sweep (line values, normal derivatives and time-limiter weight) and the
 // tangential sweep with the fluxes, on smooth and discontinuous data, both branches of the hybrid
-// switch, characteristic and component-wise.  Prints one line per property: name, worst deviation
+// switch, characteristic and component-wise; and the Gauss-point fluxes, time derivatives and DF, the
+// gas-kinetic ones through derivatives of moments against the micro-slopes.  Prints one line per property: name, worst deviation
 // relative to the data.  Built and run by tests/test_forms.py.
 #include <cmath>
 #include <cstdio>
@@ -102,8 +103,42 @@ static void sweeps(const Coef<double>& k, double* e) {
   }
 }
 
+// Fluxes, time derivatives and DF of one Gauss point; the second form's Prim is its own.
+static void fluxes(double* e) {
+  for (int it = 0; it < 20000; ++it) {
+    Coef<double> k = coef();
+    if (it % 4 == 3) k.c1 = k.c2 = 0;  // zero collision time: exp(-inf)
+    double w[2][4], wn[2][4], wt[2][4];
+    for (int s = 0; s < 2; ++s) {
+      state(U(0.3, 2), U(-2, 2), U(-2, 2), std::pow(10.0, U(-0.5, 0.5)), w[s]);
+      for (int c = 0; c < 4; ++c) { wn[s][c] = U(-1, 1); wt[s][c] = U(-1, 1); }
+    }
+    if (it % 2) for (int c = 0; c < 4; ++c) w[1][c] = w[0][c] * (1 + 1e-3 * U(-1, 1));
+    const double dt = std::pow(10.0, U(-4, 0));
+    const Prim<double> l = prim(w[0], k), r = prim(w[1], k);
+    const cand::Prim<double> cl = cand::prim(w[0], k), cr = cand::prim(w[1], k);
+    double x[8], y[8], isl[2];
+    lf_flux<double, true>(w[0], wn[0], wt[0], w[1], wn[1], wt[1], l, r, k, x, x + 4);
+    cand::lf_flux<double, true>(w[0], wn[0], wt[0], w[1], wn[1], wt[1], cl, cr, k, y, y + 4);
+    double s = 1;
+    for (double v : y) s = std::fmax(s, std::fabs(v));
+    e[0] = std::fmax(e[0], worst(x, y, 8, s));
+    gks_point_flux<true>(wn[0], wt[0], wn[1], wt[1], l, r, dt, k, x, x + 4, isl);
+    cand::gks_flux<double, true>(w[0], wn[0], wt[0], w[1], wn[1], wt[1], cl, cr, dt, k, y, y + 4);
+    s = 1;
+    for (double v : y) s = std::fmax(s, std::fabs(v));
+    e[1] = std::fmax(e[1], worst(x, y, 8, s));
+    const double df = cand::df_factor(cl, cr);
+    const double d[3] = {df_factor(l, r), df_factor(l, r, k), df_factor_gks(l, r, isl, k)}, ref[3] = {df, df, df};
+    e[2] = std::fmax(e[2], worst(d, ref, 3, 1.0));
+  }
+}
+
 int main() {
   const Coef<double> k = coef();
+  double g[3] = {0, 0, 0};
+  fluxes(g);
+  std::printf("flux_lf %.3e\nflux_gks %.3e\nflux_df %.3e\n", g[0], g[1], g[2]);
   double e[3] = {0, 0, 0}, f[3] = {0, 0, 0};
   sweeps<true>(k, e);
   sweeps<false>(k, f);

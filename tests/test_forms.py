@@ -1,10 +1,11 @@
-"""The difference form of the reconstruction that the FP64 kernels run against the candidate form
+"""The forms of reconstruction and fluxes that the FP64 kernels run against the candidate forms
 that the FP32 kernels run, both in FP64 on the host (``tests/forms_check.cpp``).
 
 Tolerance: both forms evaluate the same polynomial from the same averages; with sound speeds of
 order one to ten the projections amplify a rounding of the data (1.1e-16 of its maximum) by up to
 about 1e3, so 1e-12 of the data.  The limiter weight is compared where the indicators stand clear
-of rounding (jumps and independent states)."""
+of rounding (jumps and independent states).  Fluxes are compared relative to the largest of their
+values at the point, where the moments' cancellations cost about the same."""
 import os
 import subprocess
 
@@ -25,6 +26,7 @@ def worst(tmp_path_factory):
     return {ln.split()[0]: float(ln.split()[1]) for ln in out}
 
 
-@pytest.mark.parametrize("name", [a + b for a in ("normal", "omega", "tangential") for b in ("_char", "_comp")])
-def test_difference_form_equals_candidate_form(worst, name):
+@pytest.mark.parametrize("name", [a + b for a in ("normal", "omega", "tangential") for b in ("_char", "_comp")] +
+                         ["flux_lf", "flux_gks", "flux_df"])
+def test_fp64_forms_equal_candidate_forms(worst, name):
     assert worst[name] < (1e-10 if name.startswith("omega") else 1e-12), worst
