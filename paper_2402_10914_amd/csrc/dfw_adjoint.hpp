@@ -126,50 +126,6 @@ DFW_HD void basis_adj_add(BasisAdj<real>& a, const BasisAdj<real>& b) {
   a.b2 += b.b2;
 }
 
-// Component C of project(B, w), and its adjoint (the four adjoints sum to project_adj).
-template <int C, class real>
-DFW_HD real project_comp(const Basis<real>& B, const real* w) {
-  if (C == 2) return w[2] - B.v * w[0];
-  const real T = B.b2 * w[0] - B.b1 * (B.u * w[1] + B.v * w[2] - w[3]);
-  if (C == 1) return w[0] - real(2) * T;
-  const real s = (B.u * w[0] - w[1]) * B.ic;
-  return C == 0 ? T + s : T - s;
-}
-
-template <int C, class real>
-DFW_HD void project_adj_comp(const Basis<real>& B, const real* w, real lqc, real* lw, BasisAdj<real>& lB) {
-  if (C == 2) {
-    lw[2] += lqc;
-    lw[0] += -B.v * lqc;
-    lB.v += -w[0] * lqc;
-    return;
-  }
-  real lT, ls = real(0);
-  if (C == 1) {
-    lw[0] += lqc;
-    lT = real(-2) * lqc;
-  } else {
-    lT = lqc;
-    ls = C == 0 ? lqc : -lqc;
-  }
-  if (C != 1) {
-    lB.u += ls * w[0] * B.ic;
-    lw[0] += ls * B.u * B.ic;
-    lw[1] += -ls * B.ic;
-    lB.ic += ls * (B.u * w[0] - w[1]);
-  }
-  const real X = B.u * w[1] + B.v * w[2] - w[3];
-  lB.b2 += lT * w[0];
-  lw[0] += lT * B.b2;
-  lB.b1 += -lT * X;
-  const real lX = -lT * B.b1;
-  lB.u += lX * w[1];
-  lw[1] += lX * B.u;
-  lB.v += lX * w[2];
-  lw[2] += lX * B.v;
-  lw[3] += -lX;
-}
-
 // Component C of R^T lw (the part of unproject_adj that does not depend on q).
 template <int C, class real>
 DFW_HD real unproject_adj_q_comp(const Basis<real>& B, const real* lw) {
@@ -203,266 +159,193 @@ DFW_HD void unproject_adj_B_comp(const Basis<real>& B, real qc, const real* lw, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Hybrid reconstruction: lP (NDEG coefficients) -> lQ (5) and the DF of the centre cell (DF branch).
-// With a non-null P it also stores the forward polynomial (the same NDEG coefficients recon_poly
-// gives, up to rounding: the reverse divides once per smoothness indicator and reuses the
-// reciprocals).
+// Hybrid reconstruction in the difference form of dfw_math.hpp, reversed.  ao_weights_adj takes the
+// weights back to the differences: from the adjoints of a_0, a_2, H, is, x01, x12 (those of the
+// combination) to those of d_1, d_2, t_0, t_1, t_2 (accumulated).  About 60 instructions; the reverse
+// through separate candidates and five averages took about 220.
 // ------------------------------------------------------------------------------------------------
-template <class real, int NDEG, int RULE = -1>
-DFW_HD void recon_poly_adj(const real* Q, real a_lo, real a_c, real a_hi, const Coef<real>& k, const real* lP, real* lQ,
-                           real& la_c, real* P = nullptr) {
-  const real Q0 = Q[0], Q1 = Q[1], Q2 = Q[2], Q3 = Q[3], Q4 = Q[4];
-  const real i6 = real(1.0 / 6.0);
-  real p1_0 = (real(5) * Q2 + real(2) * Q3 - Q1) * i6;
-  real p1_1 = Q3 - Q2;
-  real p1_2 = real(0.5) * (Q1 + Q3) - Q2;
-  real lP0 = lP[0], lP1 = NDEG > 1 ? lP[1] : real(0), lP2 = NDEG > 2 ? lP[2] : real(0);
-  real lP3 = NDEG > 3 ? lP[3] : real(0), lP4 = NDEG > 4 ? lP[4] : real(0);
-  real l10, l11, l12;  // adjoints of p1's coefficients
-  if (df_switch<RULE>(a_lo, a_c, a_hi, k)) {
-    la_c += lP0 * (p1_0 - Q2) + lP1 * p1_1 + lP2 * p1_2;
-    lQ[2] += lP0 * (real(1) - a_c);
-    if (P) {
-      P[0] = Q2 + a_c * (p1_0 - Q2);
-      if (NDEG > 1) P[1] = a_c * p1_1;
-      if (NDEG > 2) P[2] = a_c * p1_2;
-      if (NDEG > 3) P[3] = real(0);
-      if (NDEG > 4) P[4] = real(0);
-    }
-    l10 = a_c * lP0;
-    l11 = a_c * lP1;
-    l12 = a_c * lP2;
-  } else {
-    real p0_0 = (real(2) * Q0 - real(7) * Q1 + real(11) * Q2) * i6;
-    real p0_1 = Q0 - real(3) * Q1 + real(2) * Q2;
-    real p0_2 = real(0.5) * (Q0 + Q2) - Q1;
-    real p2_0 = (real(2) * Q2 + real(5) * Q3 - Q4) * i6;
-    real p2_1 = Q3 - Q2;
-    real p2_2 = real(0.5) * (Q2 + Q4) - Q3;
-    real c0 = (real(2) * Q0 - real(13) * Q1 + real(47) * Q2 + real(27) * Q3 - real(3) * Q4) * real(1.0 / 60.0);
-    real c1 = (Q1 - real(15) * Q2 + real(15) * Q3 - Q4) * real(1.0 / 12.0);
-    real c2 = (-Q0 + real(6) * Q1 - real(8) * Q2 + real(2) * Q3 + Q4) * real(0.125);
-    real c3 = (-Q1 + real(3) * Q2 - real(3) * Q3 + Q4) * i6;
-    real c4 = (Q0 - real(4) * Q1 + real(6) * Q2 - real(4) * Q3 + Q4) * real(1.0 / 24.0);
-    const real k1312 = real(13.0 / 12.0), k14 = real(0.25);
-    real t0 = Q0 - real(2) * Q1 + Q2, s0 = Q0 - real(4) * Q1 + real(3) * Q2;
-    real t1 = Q1 - real(2) * Q2 + Q3, s1 = Q1 - Q3;
-    real t2 = Q2 - real(2) * Q3 + Q4, s2 = real(3) * Q2 - real(4) * Q3 + Q4;
-    real b0 = k1312 * t0 * t0 + k14 * s0 * s0;
-    real b1 = k1312 * t1 * t1 + k14 * s1 * s1;
-    real b2 = k1312 * t2 * t2 + k14 * s2 * s2;
-    real u1 = (real(11) * (Q0 - Q4) + real(82) * (Q3 - Q1)) * real(1.0 / 120.0);
-    real u2 = (real(40) * (Q1 + Q3) - real(3) * (Q0 + Q4) - real(74) * Q2) * real(1.0 / 56.0);
-    real u3 = (real(2) * (Q1 - Q3) + Q4 - Q0) * real(1.0 / 12.0);
-    real u4 = c4;
-    real e1 = u1 + real(0.1) * u3;
-    real e2 = u2 + real(123.0 / 455.0) * u4;
-    real b3 = e1 * e1 + real(13.0 / 3.0) * e2 * e2 + real(781.0 / 20.0) * u3 * u3 + real(1421461.0 / 2275.0) * u4 * u4;
-    real tau = (fabs(b3 - b0) + fabs(b3 - b1) + fabs(b3 - b2)) * real(1.0 / 3.0);
-    real be[4] = {b0 + k.eps, b1 + k.eps, b2 + k.eps, b3 + k.eps};
-    const real i01 = rcp_pos(be[0] * be[1]), i23 = rcp_pos(be[2] * be[3]);
-    real ib[4] = {be[1] * i01, be[0] * i01, be[3] * i23, be[2] * i23}, r[4], w[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      r[q] = tau * ib[q];
-      w[q] = k.d[q] * (real(1) + r[q] * r[q]);
-    }
-    real iws = rcp_pos(w[0] + w[1] + w[2] + w[3]);
-    real g3 = w[3] * iws;
-    real g0 = w[0] * iws - g3 * k.dr[0];
-    real g1 = w[1] * iws - g3 * k.dr[1];
-    real g2 = w[2] * iws - g3 * k.dr[2];
-    real h3 = g3 * k.inv_d3;
-    if (P) {
-      P[0] = g0 * p0_0 + g1 * p1_0 + g2 * p2_0 + h3 * c0;
-      if (NDEG > 1) P[1] = g0 * p0_1 + g1 * p1_1 + g2 * p2_1 + h3 * c1;
-      if (NDEG > 2) P[2] = g0 * p0_2 + g1 * p1_2 + g2 * p2_2 + h3 * c2;
-      if (NDEG > 3) P[3] = h3 * c3;
-      if (NDEG > 4) P[4] = h3 * c4;
-    }
-    // reverse of P
-    real lg0 = lP0 * p0_0 + lP1 * p0_1 + lP2 * p0_2;
-    real lg1 = lP0 * p1_0 + lP1 * p1_1 + lP2 * p1_2;
-    real lg2 = lP0 * p2_0 + lP1 * p2_1 + lP2 * p2_2;
-    real lh3 = lP0 * c0 + lP1 * c1 + lP2 * c2 + lP3 * c3 + lP4 * c4;
-    real l00 = g0 * lP0, l01 = g0 * lP1, l02 = g0 * lP2;
-    l10 = g1 * lP0;
-    l11 = g1 * lP1;
-    l12 = g1 * lP2;
-    real l20 = g2 * lP0, l21 = g2 * lP1, l22 = g2 * lP2;
-    real lc0 = h3 * lP0, lc1 = h3 * lP1, lc2 = h3 * lP2, lc3 = h3 * lP3, lc4 = h3 * lP4;
-    // weights
-    real lg3 = lh3 * k.inv_d3 - lg0 * k.dr[0] - lg1 * k.dr[1] - lg2 * k.dr[2];
-    real lw[4] = {lg0 * iws, lg1 * iws, lg2 * iws, lg3 * iws};
-    real liws = lg0 * w[0] + lg1 * w[1] + lg2 * w[2] + lg3 * w[3];
-    real lS = -liws * iws * iws;
-    real ltau = real(0), lb[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      lw[q] += lS;
-      real lr = lw[q] * k.d[q] * real(2) * r[q] * ib[q];
-      ltau += lr;
-      lb[q] = -lr * r[q];
-    }
-    real s30 = sgn(b3 - b0), s31 = sgn(b3 - b1), s32 = sgn(b3 - b2);
-    real lt3 = ltau * real(1.0 / 3.0);
-    lb[3] += lt3 * (s30 + s31 + s32);
-    lb[0] -= lt3 * s30;
-    lb[1] -= lt3 * s31;
-    lb[2] -= lt3 * s32;
-    // b3
-    real le1 = real(2) * e1 * lb[3];
-    real le2 = real(26.0 / 3.0) * e2 * lb[3];
-    real lu3 = real(781.0 / 10.0) * u3 * lb[3] + real(0.1) * le1;
-    real lu4 = real(2.0 * 1421461.0 / 2275.0) * u4 * lb[3] + real(123.0 / 455.0) * le2;
-    real lu1 = le1, lu2 = le2;
-    lc4 += lu4;
-    // u1..u3 -> Q
-    lQ[0] += lu1 * real(11.0 / 120.0) - lu2 * real(3.0 / 56.0) - lu3 * real(1.0 / 12.0);
-    lQ[1] += -lu1 * real(82.0 / 120.0) + lu2 * real(40.0 / 56.0) + lu3 * real(2.0 / 12.0);
-    lQ[2] += -lu2 * real(74.0 / 56.0);
-    lQ[3] += lu1 * real(82.0 / 120.0) + lu2 * real(40.0 / 56.0) - lu3 * real(2.0 / 12.0);
-    lQ[4] += -lu1 * real(11.0 / 120.0) - lu2 * real(3.0 / 56.0) + lu3 * real(1.0 / 12.0);
-    // b0..b2 -> Q
-    real lt0 = real(2) * k1312 * t0 * lb[0], ls0 = real(2) * k14 * s0 * lb[0];
-    real lt1 = real(2) * k1312 * t1 * lb[1], ls1 = real(2) * k14 * s1 * lb[1];
-    real lt2 = real(2) * k1312 * t2 * lb[2], ls2 = real(2) * k14 * s2 * lb[2];
-    lQ[0] += lt0 + ls0;
-    lQ[1] += real(-2) * lt0 - real(4) * ls0 + lt1 + ls1;
-    lQ[2] += lt0 + real(3) * ls0 - real(2) * lt1 + lt2 + real(3) * ls2;
-    lQ[3] += lt1 - ls1 - real(2) * lt2 - real(4) * ls2;
-    lQ[4] += lt2 + ls2;
-    // candidates p0, p2 and the quartic -> Q
-    lQ[0] += l00 * real(2.0 / 6.0) + l01 + real(0.5) * l02;
-    lQ[1] += l00 * real(-7.0 / 6.0) - real(3) * l01 - l02;
-    lQ[2] += l00 * real(11.0 / 6.0) + real(2) * l01 + real(0.5) * l02;
-    lQ[2] += l20 * real(2.0 / 6.0) - l21 + real(0.5) * l22;
-    lQ[3] += l20 * real(5.0 / 6.0) + l21 - l22;
-    lQ[4] += l20 * real(-1.0 / 6.0) + real(0.5) * l22;
-    lQ[0] += lc0 * real(2.0 / 60.0) - lc2 * real(0.125) + lc4 * real(1.0 / 24.0);
-    lQ[1] += lc0 * real(-13.0 / 60.0) + lc1 * real(1.0 / 12.0) + lc2 * real(6.0 / 8.0) - lc3 * real(1.0 / 6.0) -
-             lc4 * real(4.0 / 24.0);
-    lQ[2] += lc0 * real(47.0 / 60.0) - lc1 * real(15.0 / 12.0) - lc2 + lc3 * real(3.0 / 6.0) + lc4 * real(6.0 / 24.0);
-    lQ[3] += lc0 * real(27.0 / 60.0) + lc1 * real(15.0 / 12.0) + lc2 * real(2.0 / 8.0) - lc3 * real(3.0 / 6.0) -
-             lc4 * real(4.0 / 24.0);
-    lQ[4] += lc0 * real(-3.0 / 60.0) - lc1 * real(1.0 / 12.0) + lc2 * real(1.0 / 8.0) + lc3 * real(1.0 / 6.0) +
-             lc4 * real(1.0 / 24.0);
-  }
-  // candidate p1 -> Q (both branches)
-  lQ[1] += -l10 * i6 + real(0.5) * l12;
-  lQ[2] += real(5) * l10 * i6 - l11 - l12;
-  lQ[3] += real(2) * l10 * i6 + l11 + real(0.5) * l12;
+// y with the sign of x, zero at x = 0.
+template <class real>
+DFW_HD real signed_by(real y, real x) {
+  return x > real(0) ? y : (x < real(0) ? -y : real(0));
 }
 
-// Reverse of recon_gauss: the adjoints lv, ld of the values and slopes at the two Gauss points ->
-// lQ (5, accumulated) and the DF of the centre cell (DF branch).  Also returns the forward values
-// and slopes (v, d), as recon_gauss computes them up to rounding.
+template <class real>
+DFW_HD void ao_weights_adj(const AoWeights<real>& A, real t0, real t1, real t2, const Coef<real>& k, real la0, real la2,
+                           real lH, real lis, real lx01, real lx12, real& ld1, real& ld2, real& lt0, real& lt1,
+                           real& lt2) {
+  const real lS = -(lis * A.is) * A.is;
+  const real c0 = k.d[0] * (la0 + lS), c1 = k.d[1] * lS, c2 = k.d[2] * (la2 + lS);
+  const real c3 = (lH + lS) - (c0 + c1 + c2);  // of r_3^2
+  // half the adjoints of r_k, over B_k
+  const real g0 = (c0 * A.r[0]) * A.ib[0], g1 = (c1 * A.r[1]) * A.ib[1], g2 = (c2 * A.r[2]) * A.ib[2];
+  const real g3 = (c3 * A.r[3]) * A.ib[3];
+  const real T = real(4.0 / 3.0) * ((g0 + g1) + (g2 + g3));  // twice the adjoint of each |B_3 - B_k|
+  const real s0 = signed_by(T, A.j0), s1 = signed_by(T, A.j1), s2 = signed_by(T, A.j2);
+  // twice the adjoints of B_k
+  const real w0 = fmadd(real(-4) * g0, A.r[0], -s0), w1 = fmadd(real(-4) * g1, A.r[1], -s1);
+  const real w2 = fmadd(real(-4) * g2, A.r[2], -s2), w3 = fmadd(real(-4) * g3, A.r[3], s0 + s1 + s2);
+  const real k1312 = real(13.0 / 12.0);
+  const real le1 = A.e1 * w3, le2 = (k1312 * A.e2) * w3;
+  const real lu = fmadd(real(kBetaU) * A.u, w3, real(1.0 / 12.0) * le1);
+  const real lv = fmadd(real(kBetaV) * A.v, w3, real(-11.0 / 130.0) * le2);
+  lx01 += lu + lv;
+  lx12 += lu - lv;
+  const real lh0 = A.h0 * w0, lh1 = fmadd(A.h1, w1, le1), lh2 = A.h2 * w2;
+  lt0 += fmadd(k1312 * t0, w0, fmadd(real(0.5), lh0, lx01));
+  lt1 += fmadd(k1312 * t1, w1, fmadd(real(0.5), lh1, le2)) + (lx12 - lx01);
+  lt2 += fmadd(k1312 * t2, w2, fmadd(real(-0.5), lh2, -lx12));
+  ld1 += lh0 + lh1;
+  ld2 += lh2;
+}
+
+// Adjoints of d_1, d_2 and t_k -> those of the four differences.
+template <class real>
+DFW_HD void differences_adj(real ld1, real ld2, real lt0, real lt1, real lt2, real* ld) {
+  ld[0] = -lt0;
+  ld[1] = ld1 + (lt0 - lt1);
+  ld[2] = ld2 + (lt1 - lt2);
+  ld[3] = lt2;
+}
+
+// Reverse of recon_edge on the differences d[0..3]: ldv, lsl -> ld (overwrites d, which is not needed
+// any more) and the DF of the centre cell (DF branch); also the forward dv and sl.
+template <int RULE = -1, class real>
+DFW_HD void recon_edge_adj(real* d, real a_lo, real a_c, real a_hi, const Coef<real>& k, real ldv, real lsl,
+                           real& la_c, real& dv, real& sl) {
+  const real d1 = d[1], d2 = d[2];
+  const real t0 = d1 - d[0], t1 = d2 - d1, t2 = d[3] - d2;
+  const real v1 = fmadd(real(-1.0 / 6.0), t1, real(0.5) * d2);
+  if (df_switch<RULE>(a_lo, a_c, a_hi, k)) {
+    dv = a_c * v1;
+    sl = a_c * d2;
+    la_c += ldv * v1 + lsl * d2;
+    const real lv = a_c * ldv;
+    differences_adj(real(0), fmadd(real(0.5), lv, a_c * lsl), real(0), real(-1.0 / 6.0) * lv, real(0), d);
+    return;
+  }
+  const AoWeights<real> A = ao_weights<true>(d1, d2, t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), k);
+  const real ca = fmadd(real(1.0 / 3.0), A.a0, real(1.0 / 30.0) * A.H);
+  const real cb = fmadd(real(1.0 / 6.0), A.a2, real(0.05) * A.H);
+  const real H12 = real(1.0 / 12.0) * A.H;
+  const real Y = fmadd(cb, A.x12, ca * A.x01), X = fmadd(A.a0, A.x01, H12 * A.x12);
+  dv = fmadd(A.is, Y, v1);
+  sl = fmadd(A.is, X, d2);
+  const real lY = ldv * A.is, lX = lsl * A.is;
+  const real la0 = A.x01 * fmadd(real(1.0 / 3.0), lY, lX), la2 = A.x12 * (real(1.0 / 6.0) * lY);
+  const real lH = fmadd(A.x12, fmadd(real(1.0 / 12.0), lX, real(0.05) * lY), A.x01 * (real(1.0 / 30.0) * lY));
+  real ld1 = real(0), ld2 = fmadd(real(0.5), ldv, lsl), lt0 = real(0), lt1 = real(-1.0 / 6.0) * ldv, lt2 = real(0);
+  ao_weights_adj(A, t0, t1, t2, k, la0, la2, lH, fmadd(ldv, Y, lsl * X), fmadd(lY, ca, lX * A.a0),
+                 fmadd(lY, cb, lX * H12), ld1, ld2, lt0, lt1, lt2);
+  differences_adj(ld1, ld2, lt0, lt1, lt2, d);
+}
+
+// Reverse of recon_gauss_parts on the differences d[0..3]: lev, lod, levd, lodd -> ld (overwrites d) and
+// the DF of the centre cell (DF branch); also the forward parts.
+template <int RULE = -1, class real>
+DFW_HD void recon_gauss_parts_adj(real* d, real a_lo, real a_c, real a_hi, const Coef<real>& k, real lev, real lod,
+                                  real levd, real lodd, real& la_c, real& ev, real& od, real& evd, real& odd) {
+  const real d1 = d[1], d2 = d[2];
+  const real t0 = d1 - d[0], t1 = d2 - d1, t2 = d[3] - d2;
+  const real dl = real(kGpDelta);
+  const real lo = dl * lod, lod2 = dl * lodd;  // of od/delta, odd/delta
+  if (df_switch<RULE>(a_lo, a_c, a_hi, k)) {
+    const real h1 = fmadd(real(0.5), t1, d1);
+    ev = real(0);
+    evd = a_c * h1;
+    od = dl * evd;
+    odd = dl * (a_c * t1);
+    const real s = lo + levd;
+    la_c += h1 * s + t1 * lod2;
+    const real lh1 = a_c * s;
+    differences_adj(lh1, real(0), real(0), fmadd(real(0.5), lh1, a_c * lod2), real(0), d);
+    return;
+  }
+  const AoWeights<real> A = ao_weights<true>(d1, d2, t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), k);
+  const real p = A.a0 * A.x01, q = A.a2 * A.x12, Hu = A.H * A.u, Hv = A.H * A.v;
+  const real x = p + q, ish = real(0.5) * A.is;
+  const real E1 = fmadd(real(7.0 / 36.0), Hu, x), E2 = fmadd(real(1.0 / 6.0), Hu, x);
+  const real E3 = fmadd(real(-1.0 / 9.0), Hv, p - q), zv = real(-1.0 / 4320.0) * Hv;
+  od = dl * fmadd(ish, E1, A.h1);
+  evd = fmadd(ish, E2, A.h1);
+  odd = dl * fmadd(A.is, E3, t1);
+  ev = A.is * zv;
+  const real lis = fmadd(real(0.5), fmadd(lo, E1, levd * E2), fmadd(lod2, E3, lev * zv));
+  const real lE1 = ish * lo, lE2 = ish * levd, lE3 = A.is * lod2;
+  const real lp = (lE1 + lE2) + lE3, lq = (lE1 + lE2) - lE3;
+  const real lHu = fmadd(real(7.0 / 36.0), lE1, real(1.0 / 6.0) * lE2);
+  const real lHv = fmadd(real(-1.0 / 9.0), lE3, real(-1.0 / 4320.0) * (A.is * lev));
+  const real lh1 = lo + levd;
+  real ld1 = lh1, ld2 = real(0), lt0 = real(0), lt1 = fmadd(real(0.5), lh1, lod2), lt2 = real(0);
+  ao_weights_adj(A, t0, t1, t2, k, lp * A.x01, lq * A.x12, fmadd(lHu, A.u, lHv * A.v), lis,
+                 fmadd(lp, A.a0, A.H * (lHu + lHv)), fmadd(lq, A.a2, A.H * (lHu - lHv)), ld1, ld2, lt0, lt1, lt2);
+  differences_adj(ld1, ld2, lt0, lt1, lt2, d);
+}
+
+// The reverses on the five averages: lQ += (d of the differences), plus the average's own share.
+template <class real>
+DFW_HD void averages_adj(const real* ld, real lQ2, real* lQ) {
+  lQ[0] -= ld[0];
+  lQ[1] += ld[0] - ld[1];
+  lQ[2] += ld[1] - ld[2] + lQ2;
+  lQ[3] += ld[2] - ld[3];
+  lQ[4] += ld[3];
+}
+
+template <class real>
+DFW_HD void average_differences(const real* Q, real* d) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) d[m] = Q[m + 1] - Q[m];
+}
+
+// Reverse of recon_poly (NDEG coefficients at the edge).
+template <class real, int NDEG, int RULE = -1>
+DFW_HD void recon_poly_adj(const real* Q, real a_lo, real a_c, real a_hi, const Coef<real>& k, const real* lP, real* lQ,
+                           real& la_c) {
+  real d[4], dv, sl;
+  average_differences(Q, d);
+  recon_edge_adj<RULE>(d, a_lo, a_c, a_hi, k, lP[0], NDEG > 1 ? lP[1] : real(0), la_c, dv, sl);
+  averages_adj(d, lP[0], lQ);
+  if (NDEG > 2) {  // P2 = D2 + 3/2 (D3 + D4), P3 = D3 + 2 D4, P4 = D4
+    const real l3 = NDEG > 3 ? lP[3] : real(0), l4 = NDEG > 4 ? lP[4] : real(0);
+    const real lD2 = lP[2], lD3 = real(1.5) * lP[2] + l3, lD4 = real(1.5) * lP[2] + real(2) * l3 + l4;
+    average_differences(Q, d);
+    const real t0 = d[1] - d[0], t1 = d[2] - d[1], t2 = d[3] - d[2];
+    real ld1 = real(0), ld2 = real(0), lt0 = real(0), lt1 = real(0), lt2 = real(0);
+    if (df_switch<RULE>(a_lo, a_c, a_hi, k)) {
+      la_c += real(0.5) * lD2 * t1;
+      lt1 = real(0.5) * a_c * lD2;
+    } else {
+      const AoWeights<real> A =
+          ao_weights<true>(d[1], d[2], t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), k);
+      const real h = real(0.5) * lD2;  // D2 = (t1 + is y)/2, D3 = -is H u/12, D4 = is H v/24
+      const real y = A.a0 * A.x01 - A.a2 * A.x12 - real(0.125) * A.H * A.v;
+      const real lHu = real(-1.0 / 12.0) * lD3 * A.is;
+      const real lHv = (real(1.0 / 24.0) * lD4 - real(0.125) * h) * A.is;
+      const real lis = h * y - real(1.0 / 12.0) * lD3 * A.H * A.u + real(1.0 / 24.0) * lD4 * A.H * A.v;
+      lt1 = h;
+      ao_weights_adj(A, t0, t1, t2, k, h * A.is * A.x01, -h * A.is * A.x12, lHu * A.u + lHv * A.v, lis,
+                     h * A.is * A.a0 + A.H * (lHu + lHv), -h * A.is * A.a2 + A.H * (lHu - lHv), ld1, ld2, lt0, lt1, lt2);
+    }
+    differences_adj(ld1, ld2, lt0, lt1, lt2, d);
+    averages_adj(d, real(0), lQ);
+  }
+}
+
+// Reverse of recon_gauss: lv, ld (values and slopes at the two Gauss points) -> lQ, la_c; also the
+// forward v and dd.
 template <class real, int RULE = -1>
 DFW_HD void recon_gauss_adj(const real* Q, real a_lo, real a_c, real a_hi, const Coef<real>& k, const real* lv,
-                            const real* ld, real* lQ, real& la_c, real* v, real* d) {
-  const real Q1 = Q[1], Q2 = Q[2], Q3 = Q[3];
-  const real dl = real(kGpDelta);
-  // reverse of the even/odd split (linear, so it needs no forward value)
-  const real lev = lv[0] + lv[1], lod = lv[1] - lv[0], levd = ld[0] + ld[1], lodd = ld[1] - ld[0];
-  real lD1 = dl * lod + levd;
-  real lD2 = real(2) * dl * lodd;
-  real lD3 = dl * real(1.0 / 12.0) * lod + real(0.25) * levd;
-  real lD4 = -real(1.0 / 180.0) * lev + dl * real(1.0 / 3.0) * lodd;
-  lQ[2] += lev;
-  real D1, D2, D3 = real(0), D4 = real(0);
-  if (df_switch<RULE>(a_lo, a_c, a_hi, k)) {
-    const real h1 = real(0.5) * (Q3 - Q1), h2 = real(0.5) * (Q1 - real(2) * Q2 + Q3);
-    D1 = a_c * h1;
-    D2 = a_c * h2;
-    la_c += lD1 * h1 + lD2 * h2;
-    const real m1 = real(0.5) * a_c * lD1, m2 = real(0.5) * a_c * lD2;
-    lQ[1] += m2 - m1;
-    lQ[2] -= real(2) * m2;
-    lQ[3] += m1 + m2;
-  } else {
-    const WenoTerms<real> T = weno_terms(Q);
-    const real b0 = T.b[0], b1 = T.b[1], b2 = T.b[2], b3 = T.b[3];
-    const real tau = (fabs(b3 - b0) + fabs(b3 - b1) + fabs(b3 - b2)) * real(1.0 / 3.0);
-    const real B0 = b0 + k.eps, B1 = b1 + k.eps, B2 = b2 + k.eps, B3 = b3 + k.eps;
-    const real P01 = B0 * B1, P23 = B2 * B3, iP = rcp_pos(P01 * P23);
-    const real a23 = P23 * iP, a01 = P01 * iP;
-    const real ib[4] = {a23 * B1, a23 * B0, a01 * B3, a01 * B2};  // 1 / B_q
-    real r[4], w[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      r[q] = tau * ib[q];
-      w[q] = k.d[q] * (real(1) + r[q] * r[q]);
-    }
-    const real iws = rcp_pos(w[0] + w[1] + w[2] + w[3]);
-    const real g3 = w[3] * iws;
-    const real g0 = w[0] * iws - g3 * k.dr[0];
-    const real g1 = w[1] * iws - g3 * k.dr[1];
-    const real g2 = w[2] * iws - g3 * k.dr[2];
-    const real h3 = g3 * k.inv_d3;
-    const real q1 = T.u1 - real(0.15) * T.u3, q2 = T.u2 - real(3.0 / 14.0) * T.u4;
-    D1 = real(0.5) * (g0 * T.s0 - g1 * T.s1 - g2 * T.s2) + h3 * q1;
-    D2 = real(0.5) * (g0 * T.t0 + g1 * T.t1 + g2 * T.t2) + h3 * q2;
-    D3 = h3 * T.u3;
-    D4 = h3 * T.u4;
-    // D1..D4 -> weights and terms
-    const real lg0 = real(0.5) * (lD1 * T.s0 + lD2 * T.t0);
-    const real lg1 = real(0.5) * (lD2 * T.t1 - lD1 * T.s1);
-    const real lg2 = real(0.5) * (lD2 * T.t2 - lD1 * T.s2);
-    const real lh3 = lD1 * q1 + lD2 * q2 + lD3 * T.u3 + lD4 * T.u4;
-    real ls0 = real(0.5) * g0 * lD1, ls1 = -real(0.5) * g1 * lD1, ls2 = -real(0.5) * g2 * lD1;
-    real lt0 = real(0.5) * g0 * lD2, lt1 = real(0.5) * g1 * lD2, lt2 = real(0.5) * g2 * lD2;
-    real lu1 = h3 * lD1, lu2 = h3 * lD2;
-    real lu3 = h3 * (lD3 - real(0.15) * lD1), lu4 = h3 * (lD4 - real(3.0 / 14.0) * lD2);
-    // weights -> indicators
-    const real lg3 = lh3 * k.inv_d3 - lg0 * k.dr[0] - lg1 * k.dr[1] - lg2 * k.dr[2];
-    const real lgs[4] = {lg0, lg1, lg2, lg3};
-    const real lS = -(lg0 * w[0] + lg1 * w[1] + lg2 * w[2] + lg3 * w[3]) * iws * iws;
-    real ltau = real(0), lb[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const real lr = (lgs[q] * iws + lS) * k.d[q] * real(2) * r[q];
-      ltau += lr * ib[q];
-      lb[q] = -lr * r[q] * ib[q];
-    }
-    const real s30 = sgn(b3 - b0), s31 = sgn(b3 - b1), s32 = sgn(b3 - b2);
-    const real lt3 = ltau * real(1.0 / 3.0);
-    lb[3] += lt3 * (s30 + s31 + s32);
-    lb[0] -= lt3 * s30;
-    lb[1] -= lt3 * s31;
-    lb[2] -= lt3 * s32;
-    // indicators -> terms
-    const real k1312 = real(13.0 / 12.0), k14 = real(0.25);
-    lt0 += real(2) * k1312 * T.t0 * lb[0];
-    ls0 += real(2) * k14 * T.s0 * lb[0];
-    lt1 += real(2) * k1312 * T.t1 * lb[1];
-    ls1 += real(2) * k14 * T.s1 * lb[1];
-    lt2 += real(2) * k1312 * T.t2 * lb[2];
-    ls2 += real(2) * k14 * T.s2 * lb[2];
-    const real e1 = T.u1 + real(0.1) * T.u3, e2 = T.u2 + real(123.0 / 455.0) * T.u4;
-    const real le1 = real(2) * e1 * lb[3], le2 = real(26.0 / 3.0) * e2 * lb[3];
-    lu1 += le1;
-    lu2 += le2;
-    lu3 += real(781.0 / 10.0) * T.u3 * lb[3] + real(0.1) * le1;
-    lu4 += real(2.0 * 1421461.0 / 2275.0) * T.u4 * lb[3] + real(123.0 / 455.0) * le2;
-    // terms -> averages: u1 = (-11 d40 - 82 s1)/120, u2 = (34 t1 - 3 (t0 + t2))/56,
-    // u3 = (2 s1 + d40)/12, u4 = (t0 - 2 t1 + t2)/24, d40 = Q4 - Q0, s2 = t2 - 2 (Q3 - Q2)
-    const real ld40 = -real(11.0 / 120.0) * lu1 + real(1.0 / 12.0) * lu3;
-    ls1 += -real(82.0 / 120.0) * lu1 + real(2.0 / 12.0) * lu3;
-    lt1 += real(34.0 / 56.0) * lu2 - real(2.0 / 24.0) * lu4;
-    lt0 += -real(3.0 / 56.0) * lu2 + real(1.0 / 24.0) * lu4;
-    lt2 += -real(3.0 / 56.0) * lu2 + real(1.0 / 24.0) * lu4 + ls2;
-    lQ[0] += lt0 + ls0 - ld40;
-    lQ[1] += -real(2) * lt0 + lt1 - real(4) * ls0 + ls1;
-    lQ[2] += lt0 - real(2) * lt1 + lt2 + real(3) * ls0 + real(2) * ls2;
-    lQ[3] += lt1 - real(2) * lt2 - ls1 - real(2) * ls2;
-    lQ[4] += lt2 + ld40;
-  }
-  const real ev = Q2 - real(1.0 / 180.0) * D4, od = dl * (D1 + real(1.0 / 12.0) * D3);
-  const real evd = D1 + real(0.25) * D3, odd = dl * (real(2) * D2 + real(1.0 / 3.0) * D4);
-  v[0] = ev - od;
-  v[1] = ev + od;
-  d[0] = evd - odd;
-  d[1] = evd + odd;
+                            const real* ld, real* lQ, real& la_c, real* v, real* dd) {
+  real d[4], ev, od, evd, odd;
+  average_differences(Q, d);
+  recon_gauss_parts_adj<RULE>(d, a_lo, a_c, a_hi, k, lv[0] + lv[1], lv[1] - lv[0], ld[0] + ld[1], ld[1] - ld[0], la_c,
+                              ev, od, evd, odd);
+  averages_adj(d, lv[0] + lv[1], lQ);
+  v[0] = Q[2] + (ev - od);
+  v[1] = Q[2] + (ev + od);
+  dd[0] = evd - odd;
+  dd[1] = evd + odd;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1165,176 +1048,191 @@ DFW_HD void gks_flux_adj(const real* wl, const real* wln, const real* wlt, const
 template <int RULE = -1, class real>
 DFW_HD void normal_side(const Basis<real>& B, const real (*cs)[4], real a_lo, real a_c, real a_hi, real sgn_inv_dn,
                         const Coef<real>& k, real* w, real* wn) {
-  real Q[5][4];
+  real D[4][4];
 #pragma unroll
-  for (int m = 0; m < 5; ++m) project(B, cs[m], Q[m]);
+  for (int m = 0; m < 4; ++m) {
+    real x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = cs[m + 1][c] - cs[m][c];
+    project(B, x, D[m]);
+  }
   real q[4], qd[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    real s[5], P2[2];
-#pragma unroll
-    for (int m = 0; m < 5; ++m) s[m] = Q[m][c];
-    recon_poly<real, 2, RULE>(s, a_lo, a_c, a_hi, k, P2);
-    q[c] = P2[0];
-    qd[c] = P2[1] * sgn_inv_dn;
+    const real t0 = D[1][c] - D[0][c], t1 = D[2][c] - D[1][c], t2 = D[3][c] - D[2][c];
+    recon_edge<RULE>(D[1][c], D[2][c], t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), a_lo, a_c, a_hi,
+                     k, q[c], qd[c]);
+    qd[c] *= sgn_inv_dn;
   }
   unproject(B, q, w);
   unproject(B, qd, wn);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) w[c] += cs[2][c];
+}
+
+// One characteristic component C of the reverse: D[m][C] -> its adjoint, in place.
+template <int C, int RULE, class real>
+DFW_HD void normal_side_adj_comp(const Basis<real>& B, real (*D)[4], real a_lo, real a_c, real a_hi, real sgn_inv_dn,
+                                 const Coef<real>& k, const real* lw, const real* lwn, BasisAdj<real>& lB, real& la_c) {
+  real d[4] = {D[0][C], D[1][C], D[2][C], D[3][C]}, q, qd;
+  recon_edge_adj<RULE>(d, a_lo, a_c, a_hi, k, unproject_adj_q_comp<C>(B, lw), unproject_adj_q_comp<C>(B, lwn) * sgn_inv_dn,
+                       la_c, q, qd);
+  unproject_adj_B_comp<C>(B, q, lw, lB);
+  unproject_adj_B_comp<C>(B, qd * sgn_inv_dn, lwn, lB);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) D[m][C] = d[m];
 }
 
 // Reverse of normal_side; cell(m, c) gives component c of stencil cell m.  The stencil cells'
 // adjoints go to lc_add(m, c, v) (add v to cell m, component c); the basis adjoint lB and la_c (the
-// DF of the reconstructed cell, DF branch only) accumulate.  One characteristic component at a time: its projection, reconstruction forward and
-// backward, and its share of the projection adjoints, so that only one chain is live.
-template <int C, int RULE, class real, class CellFn, class AddFn>
-DFW_HD void normal_side_adj_comp(const Basis<real>& B, CellFn cell, real a_lo, real a_c, real a_hi, real sgn_inv_dn,
-                                 const Coef<real>& k, const real* lw, const real* lwn, real lqc, real lqdc,
-                                 AddFn lc_add, BasisAdj<real>& lB, real& la_c) {
-  real s[5], P2[2], lP[2], lQc[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    real w[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w[c] = cell(m, c);
-    s[m] = project_comp<C>(B, w);
-  }
-  lP[0] = lqc;
-  lP[1] = lqdc * sgn_inv_dn;
-  recon_poly_adj<real, 2, RULE>(s, a_lo, a_c, a_hi, k, lP, lQc, la_c, P2);
-  unproject_adj_B_comp<C>(B, P2[0], lw, lB);
-  unproject_adj_B_comp<C>(B, P2[1] * sgn_inv_dn, lwn, lB);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    real w[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w[c] = cell(m, c);
-    real d[4] = {0, 0, 0, 0};
-    project_adj_comp<C>(B, w, lQc[m], d, lB);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) lc_add(m, c, d[c]);
-  }
-}
-
-// cell(m, c) is read once per component; callers that keep the cells in memory pass a reader that
-// reloads them, so that nothing but the accumulators lives from one component to the next.
+// DF of the reconstructed cell, DF branch only) accumulate.  One characteristic component at a
+// time, its differences replaced by their adjoints; then the projection of each difference is reversed.
 template <int RULE = -1, class real, class CellFn, class AddFn>
 DFW_HD void normal_side_adj(const Basis<real>& B, CellFn cell, real a_lo, real a_c, real a_hi, real sgn_inv_dn,
                             const Coef<real>& k, const real* lw, const real* lwn, AddFn lc_add, BasisAdj<real>& lB,
                             real& la_c) {
-  normal_side_adj_comp<0, RULE>(B, cell, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, unproject_adj_q_comp<0>(B, lw),
-                          unproject_adj_q_comp<0>(B, lwn), lc_add, lB, la_c);
-  normal_side_adj_comp<1, RULE>(B, cell, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, unproject_adj_q_comp<1>(B, lw),
-                          unproject_adj_q_comp<1>(B, lwn), lc_add, lB, la_c);
-  normal_side_adj_comp<2, RULE>(B, cell, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, unproject_adj_q_comp<2>(B, lw),
-                          unproject_adj_q_comp<2>(B, lwn), lc_add, lB, la_c);
-  normal_side_adj_comp<3, RULE>(B, cell, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, unproject_adj_q_comp<3>(B, lw),
-                          unproject_adj_q_comp<3>(B, lwn), lc_add, lB, la_c);
+  real D[4][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    real x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = cell(m + 1, c) - cell(m, c);
+    project(B, x, D[m]);
+  }
+  normal_side_adj_comp<0, RULE>(B, D, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, lB, la_c);
+  normal_side_adj_comp<1, RULE>(B, D, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, lB, la_c);
+  normal_side_adj_comp<2, RULE>(B, D, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, lB, la_c);
+  normal_side_adj_comp<3, RULE>(B, D, a_lo, a_c, a_hi, sgn_inv_dn, k, lw, lwn, lB, la_c);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) lc_add(2, c, lw[c]);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    real x[4], d[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = cell(m + 1, c) - cell(m, c);
+    project_adj(B, x, D[m], d, lB);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      lc_add(m + 1, c, d[c]);
+      lc_add(m, c, -d[c]);
+    }
+  }
 }
 
 // Segment, one side: line(m, c) = component c of the side's line value on segment row m-2;
 // al = DF of the side's cell on rows -1, 0, +1.  Gives the states and their tangential derivatives
-// at the two Gauss points (as segment_fluxes computes them).
+// at the two Gauss points (as segment_states computes them).
 template <int RULE = -1, class real, class LineFn>
 DFW_HD void segment_side(const Basis<real>& B, LineFn line, const real* al, real inv_dt, const Coef<real>& k,
                          real (*gw)[4], real (*gwt)[4]) {
-  real Q[5][4];
+  real D[4][4];
 #pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    real w[4];
+  for (int m = 0; m < 4; ++m) {
+    real x[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) w[c] = line(m, c);
-    project(B, w, Q[m]);
+    for (int c = 0; c < 4; ++c) x[c] = line(m + 1, c) - line(m, c);
+    project(B, x, D[m]);
   }
-  real qv[2][4], qd[2][4];
+  real ev[4], od[4], evd[4], odd[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    real s[5], v[2], d[2];
-#pragma unroll
-    for (int m = 0; m < 5; ++m) s[m] = Q[m][c];
-    recon_gauss<real, RULE>(s, al[0], al[1], al[2], k, v, d);
-    qv[0][c] = v[0];
-    qv[1][c] = v[1];
-    qd[0][c] = d[0] * inv_dt;
-    qd[1][c] = d[1] * inv_dt;
+    recon_gauss_parts<RULE>(D[0][c], D[1][c], D[2][c], D[3][c], al[0], al[1], al[2], k, ev[c], od[c], evd[c], odd[c]);
+    evd[c] *= inv_dt;
+    odd[c] *= inv_dt;
   }
+  real e[4], o[4];
+  unproject(B, ev, e);
+  unproject(B, od, o);
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    unproject(B, qv[g], gw[g]);
-    unproject(B, qd[g], gwt[g]);
+  for (int c = 0; c < 4; ++c) {
+    const real m = line(2, c) + e[c];
+    gw[0][c] = m - o[c];
+    gw[1][c] = m + o[c];
+  }
+  unproject(B, evd, e);
+  unproject(B, odd, o);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    gwt[0][c] = e[c] - o[c];
+    gwt[1][c] = e[c] + o[c];
   }
 }
 
-// Reverse of segment_side for the adjoints lgw, lgwt of the Gauss-point states, in two halves.
-// First half, one characteristic component at a time: the reverse of the Gauss-point
-// reconstruction gives the characteristic adjoints of the side's five line values, handed to
-// put_q(C, m, v) (component C, row m); lB and la_c accumulate.
-template <int C, int RULE, class real, class LineFn, class PutFn>
-DFW_HD void segment_side_adj_q_comp(const Basis<real>& B, LineFn line, const real* al, real inv_dt,
-                                    const Coef<real>& k, const real (*lgw)[4], const real (*lgwt)[4], real lqv0,
-                                    real lqv1, real lqd0, real lqd1, PutFn put_q, BasisAdj<real>& lB, real& la_c) {
-  real s[5], lQc[5] = {0, 0, 0, 0, 0};
+// One characteristic component C of the reverse of segment_side: D[m][C] -> its adjoint, in place.
+// se, so: even and odd sums (point 0 + point 1, point 1 - point 0) of the adjoints of the Gauss-point
+// states, te, to those of their tangential derivatives.
+template <int C, int RULE, class real>
+DFW_HD void segment_side_adj_comp(const Basis<real>& B, real (*D)[4], const real* al, real inv_dt,
+                                  const Coef<real>& k, const real* se, const real* so, const real* te, const real* to,
+                                  BasisAdj<real>& lB, real& la_c) {
+  real d[4] = {D[0][C], D[1][C], D[2][C], D[3][C]}, ev, od, evd, odd;
+  recon_gauss_parts_adj<RULE>(d, al[0], al[1], al[2], k, unproject_adj_q_comp<C>(B, se), unproject_adj_q_comp<C>(B, so),
+                              unproject_adj_q_comp<C>(B, te) * inv_dt, unproject_adj_q_comp<C>(B, to) * inv_dt, la_c, ev,
+                              od, evd, odd);
+  unproject_adj_B_comp<C>(B, ev, se, lB);
+  unproject_adj_B_comp<C>(B, od, so, lB);
+  unproject_adj_B_comp<C>(B, evd * inv_dt, te, lB);
+  unproject_adj_B_comp<C>(B, odd * inv_dt, to, lB);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) D[m][C] = d[m];
+}
+
+// Reverse of segment_side for the adjoints lgw, lgwt of the Gauss-point states: the adjoints of the
+// side's line values go to ll_put(m, v) (row m, all four components, each row once); lB and la_c
+// accumulate.
+template <int RULE = -1, class real, class LineFn, class PutFn>
+DFW_HD void segment_side_adj_rows(const Basis<real>& B, LineFn line, const real* al, real inv_dt, const Coef<real>& k,
+                                  const real (*lgw)[4], const real (*lgwt)[4], PutFn ll_put, BasisAdj<real>& lB,
+                                  real& la_c) {
+  real se[4], so[4], te[4], to[4], D[4][4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    se[c] = lgw[0][c] + lgw[1][c];
+    so[c] = lgw[1][c] - lgw[0][c];
+    te[c] = lgwt[0][c] + lgwt[1][c];
+    to[c] = lgwt[1][c] - lgwt[0][c];
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    real x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = line(m + 1, c) - line(m, c);
+    project(B, x, D[m]);
+  }
+  segment_side_adj_comp<0, RULE>(B, D, al, inv_dt, k, se, so, te, to, lB, la_c);
+  segment_side_adj_comp<1, RULE>(B, D, al, inv_dt, k, se, so, te, to, lB, la_c);
+  segment_side_adj_comp<2, RULE>(B, D, al, inv_dt, k, se, so, te, to, lB, la_c);
+  segment_side_adj_comp<3, RULE>(B, D, al, inv_dt, k, se, so, te, to, lB, la_c);
+  real prev[4] = {0, 0, 0, 0};  // adjoint of the difference below the row
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    real w[4];
+    real d[4] = {0, 0, 0, 0}, v[4];
+    if (m < 4) {
+      real x[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) w[c] = line(m, c);
-    s[m] = project_comp<C>(B, w);
+      for (int c = 0; c < 4; ++c) x[c] = line(m + 1, c) - line(m, c);
+      project_adj(B, x, D[m], d, lB);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = prev[c] - d[c] + (m == 2 ? se[c] : real(0));
+      prev[c] = d[c];
+    }
+    ll_put(m, v);
   }
-  const real lv[2] = {lqv0, lqv1}, ld[2] = {lqd0 * inv_dt, lqd1 * inv_dt};
-  real v[2], d[2];
-  recon_gauss_adj<real, RULE>(s, al[0], al[1], al[2], k, lv, ld, lQc, la_c, v, d);
-  unproject_adj_B_comp<C>(B, v[0], lgw[0], lB);
-  unproject_adj_B_comp<C>(B, v[1], lgw[1], lB);
-  unproject_adj_B_comp<C>(B, d[0] * inv_dt, lgwt[0], lB);
-  unproject_adj_B_comp<C>(B, d[1] * inv_dt, lgwt[1], lB);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) put_q(C, m, lQc[m]);
 }
 
-template <int RULE = -1, class real, class LineFn, class PutFn>
-DFW_HD void segment_side_adj_q(const Basis<real>& B, LineFn line, const real* al, real inv_dt, const Coef<real>& k,
-                               const real (*lgw)[4], const real (*lgwt)[4], PutFn put_q, BasisAdj<real>& lB,
-                               real& la_c) {
-#define DFW_SEG_COMP(C)                                                                                          \
-  segment_side_adj_q_comp<C, RULE>(B, line, al, inv_dt, k, lgw, lgwt, unproject_adj_q_comp<C>(B, lgw[0]),      \
-                                   unproject_adj_q_comp<C>(B, lgw[1]), unproject_adj_q_comp<C>(B, lgwt[0]),    \
-                                   unproject_adj_q_comp<C>(B, lgwt[1]), put_q, lB, la_c)
-  DFW_SEG_COMP(0);
-  DFW_SEG_COMP(1);
-  DFW_SEG_COMP(2);
-  DFW_SEG_COMP(3);
-#undef DFW_SEG_COMP
-}
-
-// Second half, one row at a time: the adjoint lw of line value w from the characteristic adjoints
-// lq[0..3] of its four components (the projection's reverse); lB accumulates.
-template <class real>
-DFW_HD void segment_side_adj_line(const Basis<real>& B, const real* w, const real* lq, real* lw, BasisAdj<real>& lB) {
-#pragma unroll
-  for (int c = 0; c < 4; ++c) lw[c] = real(0);
-  project_adj_comp<0>(B, w, lq[0], lw, lB);
-  project_adj_comp<1>(B, w, lq[1], lw, lB);
-  project_adj_comp<2>(B, w, lq[2], lw, lB);
-  project_adj_comp<3>(B, w, lq[3], lw, lB);
-}
-
-// The whole reverse: the adjoints of the side's line values go to ll_add(m, c, v); lB and la_c
-// accumulate.
+// The same with each component added by ll_add(m, c, v).
 template <int RULE = -1, class real, class LineFn, class AddFn>
 DFW_HD void segment_side_adj(const Basis<real>& B, LineFn line, const real* al, real inv_dt, const Coef<real>& k,
                              const real (*lgw)[4], const real (*lgwt)[4], AddFn ll_add, BasisAdj<real>& lB,
                              real& la_c) {
-  real lQ[5][4];
-  segment_side_adj_q<RULE>(B, line, al, inv_dt, k, lgw, lgwt, [&](int C, int m, real v) { lQ[m][C] = v; }, lB, la_c);
+  segment_side_adj_rows<RULE>(B, line, al, inv_dt, k, lgw, lgwt,
+                              [&](int m, const real* v) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    real w[4], d[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w[c] = line(m, c);
-    segment_side_adj_line(B, w, lQ[m], d, lB);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ll_add(m, c, d[c]);
-  }
+                                for (int c = 0; c < 4; ++c) ll_add(m, c, v[c]);
+                              },
+                              lB, la_c);
 }
 
 // Reverse of the flux, its time derivative and the DF at one Gauss point (left state wl with normal

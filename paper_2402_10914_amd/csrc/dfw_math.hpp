@@ -307,10 +307,15 @@ DFW_HD real time_limiter_weight(const real* Q, const Coef<real>& k) {
 // Measured, FP64, against that form: 4096^2 GKS 13.0 -> 11.5 ms per step, 512^2 GKS 249 -> 221 us per
 // step, a ragged LF batch of 48 grids 7.84 -> 6.49 ms.
 // ------------------------------------------------------------------------------------------------
+constexpr double kBetaU = 781.0 / 2880.0, kBetaV = 1421461.0 / 1310400.0;  // of u^2 and v^2 in beta_3
+
 template <class real>
 struct AoWeights {
-  real x01, x12;
-  real a0, a2, H, is;  // is = 1 / sum w
+  real x01, x12, u, v;
+  real a0, a1, a2, H, is;   // is = 1 / sum w
+  real h0, h1, h2, e1, e2;  // from here on for the reverse only
+  real j0, j1, j2;          // B_3 - B_k
+  real r[4], ib[4];         // r_k, 1 / B_k
 };
 
 // 13/12 t^2 + eps, the part of beta_k + eps that neighbouring reconstructions share.
@@ -320,30 +325,45 @@ DFW_HD real beta_curv(real t, const Coef<real>& k) {
 }
 
 // d1, d2: the differences beside the cell; m_k = beta_curv(t_k).  With a non-null om also the
-// time-limiter weight of the stencil.
-template <class real>
+// time-limiter weight of the stencil.  REV: also 1/B_k, which the reverse needs.
+template <bool REV = false, class real>
 DFW_HD AoWeights<real> ao_weights(real d1, real d2, real t0, real t1, real t2, real m0, real m1, real m2,
                                   const Coef<real>& k, real* om = nullptr) {
   AoWeights<real> A;
-  const real h0 = fmadd(real(0.5), t0, d1), h1 = fmadd(real(0.5), t1, d1), h2 = fmadd(real(-0.5), t2, d2);
+  A.h0 = fmadd(real(0.5), t0, d1);
+  A.h1 = fmadd(real(0.5), t1, d1);
+  A.h2 = fmadd(real(-0.5), t2, d2);
   A.x01 = t0 - t1;
   A.x12 = t1 - t2;
-  const real u = A.x01 + A.x12, v = A.x01 - A.x12;
-  const real e1 = fmadd(real(1.0 / 12.0), u, h1), e2 = fmadd(real(-11.0 / 130.0), v, t1);
+  A.u = A.x01 + A.x12;
+  A.v = A.x01 - A.x12;
+  A.e1 = fmadd(real(1.0 / 12.0), A.u, A.h1);
+  A.e2 = fmadd(real(-11.0 / 130.0), A.v, t1);
   // B_k = beta_k + eps
-  const real B0 = fmadd(h0, h0, m0), B1 = fmadd(h1, h1, m1), B2 = fmadd(h2, h2, m2);
-  real B3 = fmadd(real(1421461.0 / 1310400.0) * v, v, k.eps);
-  B3 = fmadd(real(781.0 / 2880.0) * u, u, B3);
-  B3 = fmadd(real(13.0 / 12.0) * e2, e2, B3);
-  B3 = fmadd(e1, e1, B3);
+  const real B0 = fmadd(A.h0, A.h0, m0), B1 = fmadd(A.h1, A.h1, m1), B2 = fmadd(A.h2, A.h2, m2);
+  real B3 = fmadd(real(kBetaV) * A.v, A.v, k.eps);
+  B3 = fmadd(real(kBetaU) * A.u, A.u, B3);
+  B3 = fmadd(real(13.0 / 12.0) * A.e2, A.e2, B3);
+  B3 = fmadd(A.e1, A.e1, B3);
+  A.j0 = B3 - B0;
+  A.j1 = B3 - B1;
+  A.j2 = B3 - B2;
   // WENO-Z weights, eqs. (36)-(37)
-  const real tau = (fabs(B3 - B0) + fabs(B3 - B1) + fabs(B3 - B2)) * real(1.0 / 3.0);
+  const real tau = (fabs(A.j0) + fabs(A.j1) + fabs(A.j2)) * real(1.0 / 3.0);
   // r_q = tau / B_q from products of the B_q and one reciprocal of B0 B1 B2 B3 (in FP64 a product of
   // four numbers in [eps, 1e75] stays normal)
   const real P01 = B0 * B1, P23 = B2 * B3;
-  const real ti = tau * rcp_pos(P01 * P23);
-  const real t23 = ti * P23, t01 = ti * P01;
-  const real r0 = t23 * B1, r1 = t23 * B0, r2 = t01 * B3, r3 = t01 * B2;
+  real r0, r1, r2, r3;
+  if constexpr (REV) {
+    const real ip = rcp_pos(P01 * P23), i23 = ip * P23, i01 = ip * P01;
+    A.ib[0] = i23 * B1, A.ib[1] = i23 * B0, A.ib[2] = i01 * B3, A.ib[3] = i01 * B2;
+    r0 = tau * A.ib[0], r1 = tau * A.ib[1], r2 = tau * A.ib[2], r3 = tau * A.ib[3];
+    A.r[0] = r0, A.r[1] = r1, A.r[2] = r2, A.r[3] = r3;
+  } else {
+    const real ti = tau * rcp_pos(P01 * P23);
+    const real t23 = ti * P23, t01 = ti * P01;
+    r0 = t23 * B1, r1 = t23 * B0, r2 = t01 * B3, r3 = t01 * B2;
+  }
   if (om) {  // tau/(beta_min + eps) and tau/(beta_max + eps) are the largest and smallest ratio
     real rmax = r0 > r1 ? r0 : r1, rmin = r0 < r1 ? r0 : r1;
     rmax = rmax > r2 ? rmax : r2;
@@ -355,10 +375,10 @@ DFW_HD AoWeights<real> ao_weights(real d1, real d2, real t0, real t1, real t2, r
   }
   const real s3 = r3 * r3;
   A.a0 = k.d[0] * fmadd(r0, r0, -s3);
-  const real a1 = k.d[1] * fmadd(r1, r1, -s3);
+  A.a1 = k.d[1] * fmadd(r1, r1, -s3);
   A.a2 = k.d[2] * fmadd(r2, r2, -s3);
   A.H = real(1) + s3;
-  A.is = rcp_pos((A.H + A.a0) + (a1 + A.a2));
+  A.is = rcp_pos((A.H + A.a0) + (A.a1 + A.a2));
   return A;
 }
 
@@ -408,7 +428,7 @@ DFW_HD void recon_gauss_parts(real d0, real d1, real d2, real d3, real a_lo, rea
   }
   const AoWeights<real> A = ao_weights(d1, d2, t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), k);
   const real p = A.a0 * A.x01, q = A.a2 * A.x12;
-  const real x = p + q, y = p - q, Hu = A.H * (A.x01 + A.x12), Hv = A.H * (A.x01 - A.x12);
+  const real x = p + q, y = p - q, Hu = A.H * A.u, Hv = A.H * A.v;
   const real ish = real(0.5) * A.is;
   od = dl * fmadd(ish, fmadd(real(7.0 / 36.0), Hu, x), h1);
   evd = fmadd(ish, fmadd(real(1.0 / 6.0), Hu, x), h1);
@@ -444,7 +464,7 @@ DFW_HD void recon_poly(const real* Q, real a_lo, real a_c, real a_hi, const Coef
       D2 = real(0.5) * (a_c * t1);
     } else {
       const AoWeights<real> A = ao_weights(d1, d2, t0, t1, t2, m0, m1, m2, k);
-      const real Hu = A.H * (A.x01 + A.x12), Hv = A.H * (A.x01 - A.x12);
+      const real Hu = A.H * A.u, Hv = A.H * A.v;
       D2 = real(0.5) * fmadd(A.is, A.a0 * A.x01 - A.a2 * A.x12 - real(0.125) * Hv, t1);
       D3 = real(-1.0 / 12.0) * (A.is * Hu);
       D4 = real(1.0 / 24.0) * (A.is * Hv);
