@@ -357,173 +357,105 @@ struct PrimAdj {
   DFW_HD void zero() { r = ir = u = v = p = c = real(0); }
 };
 
+// With the adjoints of p and 1/rho given (the speed of sound's share already in them).
 template <class real>
-DFW_HD void prim_adj(const real* w, const Prim<real>& q, const Coef<real>& k, const PrimAdj<real>& lq, real* lw) {
-  real l_p = lq.p + lq.c * k.gamma * q.ir * real(0.5) / q.c;
-  real l_ir = lq.ir + lq.c * k.gamma * q.p * real(0.5) / q.c;
-  real l_u = lq.u - real(0.5) * k.gm1 * w[1] * l_p;
-  real l_v = lq.v - real(0.5) * k.gm1 * w[2] * l_p;
+DFW_HD void prim_adj(const real* w, const Prim<real>& q, const Coef<real>& k, const PrimAdj<real>& lq, real l_p,
+                     real l_ir, real* lw) {
+  const real hg = real(0.5) * k.gm1 * l_p;
+  const real l_u = lq.u - hg * w[1], l_v = lq.v - hg * w[2];
   lw[3] += k.gm1 * l_p;
-  lw[1] += -real(0.5) * k.gm1 * q.u * l_p + l_u * q.ir;
-  lw[2] += -real(0.5) * k.gm1 * q.v * l_p + l_v * q.ir;
+  lw[1] += l_u * q.ir - hg * q.u;
+  lw[2] += l_v * q.ir - hg * q.v;
   l_ir += l_u * w[1] + l_v * w[2];
   lw[0] += lq.r - l_ir * q.ir * q.ir;
 }
 
 template <class real>
+DFW_HD void prim_adj(const real* w, const Prim<real>& q, const Coef<real>& k, const PrimAdj<real>& lq, real* lw) {
+  const real hc = lq.c * k.gamma * real(0.5) * q.ic;
+  prim_adj(w, q, k, lq, lq.p + hc * q.ir, lq.ir + hc * q.p, lw);
+}
+
+template <class real>
 DFW_HD void df_factor_adj(const Prim<real>& L, const Prim<real>& R, real lalpha, PrimAdj<real>& lL, PrimAdj<real>& lR) {
-  real jump = fabs(L.p - R.p);
-  real icl = real(1) / L.c, icr = real(1) / R.c;
-  real dn = L.u * icl - R.u * icr;
-  real dt = L.v * icl - R.v * icr;
-  real D = jump * (real(1) / L.p + real(1) / R.p) + dn * dn + dt * dt;
-  real a = real(1) / (real(1) + D * D);
-  real lD = -real(2) * D * a * a * lalpha;
-  real ljump = lD * (real(1) / L.p + real(1) / R.p);
-  lL.p += -lD * jump / (L.p * L.p);
-  lR.p += -lD * jump / (R.p * R.p);
-  real s = sgn(L.p - R.p);
-  lL.p += s * ljump;
-  lR.p -= s * ljump;
-  real ldn = real(2) * dn * lD, ldt = real(2) * dt * lD;
-  lL.u += ldn * icl;
-  lR.u -= ldn * icr;
-  lL.v += ldt * icl;
-  lR.v -= ldt * icr;
-  real licl = ldn * L.u + ldt * L.v;
-  real licr = -(ldn * R.u + ldt * R.v);
-  lL.c += -licl * icl * icl;
-  lR.c += -licr * icr * icr;
+  const real jump = fabs(L.p - R.p);
+  const real ipl = rcp_any(L.p), ipr = rcp_any(R.p);
+  const real dn = L.u * L.ic - R.u * R.ic;
+  const real dt = L.v * L.ic - R.v * R.ic;
+  const real D = jump * (ipl + ipr) + dn * dn + dt * dt;
+  const real a = rcp_any(real(1) + D * D);
+  const real lD = -real(2) * D * (a * a) * lalpha;
+  const real sj = signed_by(lD * (ipl + ipr), L.p - R.p), lj = lD * jump;
+  lL.p += sj - lj * (ipl * ipl);
+  lR.p += -sj - lj * (ipr * ipr);
+  const real ldn = real(2) * dn * lD, ldt = real(2) * dt * lD;
+  lL.u += ldn * L.ic;
+  lR.u -= ldn * R.ic;
+  lL.v += ldt * L.ic;
+  lR.v -= ldt * R.ic;
+  lL.c -= (ldn * L.u + ldt * L.v) * (L.ic * L.ic);
+  lR.c += (ldn * R.u + ldt * R.v) * (R.ic * R.ic);
 }
 
 // ------------------------------------------------------------------------------------------------
 // Lax-Friedrichs flux with the Cauchy-Kovalevskaya time derivative.
 // ------------------------------------------------------------------------------------------------
+// In the products of the density with the derivatives, as the forward.  lwt: adjoints of W_t, null
+// for zero.
 template <class real>
 DFW_HD void euler_time_derivs_adj(const real* w, const Prim<real>& q, const real* wx, const real* wy,
-                                  const Coef<real>& k, const real* lwt_in, const real* lft, real* lw, PrimAdj<real>& lq,
+                                  const Coef<real>& k, const real* lwt, const real* lft, real* lw, PrimAdj<real>& lq,
                                   real* lwx, real* lwy) {
   // forward
-  real ke = real(0.5) * (q.u * q.u + q.v * q.v);
-  real ux = (wx[1] - q.u * wx[0]) * q.ir, vx = (wx[2] - q.v * wx[0]) * q.ir;
-  real px = k.gm1 * (wx[3] - q.u * wx[1] - q.v * wx[2] + ke * wx[0]);
-  real uy = (wy[1] - q.u * wy[0]) * q.ir, vy = (wy[2] - q.v * wy[0]) * q.ir;
-  real py = k.gm1 * (wy[3] - q.u * wy[1] - q.v * wy[2] + ke * wy[0]);
-  real rt = -(q.u * wx[0] + q.r * ux + q.v * wy[0] + q.r * vy);
-  real ut = -(q.u * ux + q.v * uy + px * q.ir);
-  real vt = -(q.u * vx + q.v * vy + py * q.ir);
-  real pt = -(q.u * px + q.v * py + k.gamma * q.p * (ux + vy));
-  real wt1 = rt * q.u + q.r * ut;
-  real wt3 = pt * k.inv_gm1 + rt * ke + q.r * (q.u * ut + q.v * vt);
-  // reverse
-  real lwt[4] = {lwt_in[0], lwt_in[1], lwt_in[2], lwt_in[3]};
-  real lut = real(0), lvt = real(0), lpt = real(0), lrt = real(0), lke = real(0);
-  // ft3 = ut (w3 + p) + u (wt3 + pt)
-  lut += lft[3] * (w[3] + q.p);
-  lw[3] += lft[3] * ut;
-  lq.p += lft[3] * ut;
-  lq.u += lft[3] * (wt3 + pt);
-  lwt[3] += lft[3] * q.u;
-  lpt += lft[3] * q.u;
-  // ft2 = wt1 v + w1 vt
-  lwt[1] += lft[2] * q.v;
-  lq.v += lft[2] * wt1;
-  lw[1] += lft[2] * vt;
-  lvt += lft[2] * w[1];
-  // ft1 = wt1 u + w1 ut + pt
-  lwt[1] += lft[1] * q.u;
-  lq.u += lft[1] * wt1;
-  lw[1] += lft[1] * ut;
-  lut += lft[1] * w[1];
-  lpt += lft[1];
-  // ft0 = wt1
-  lwt[1] += lft[0];
-  // wt3 = pt/gm1 + rt ke + r (u ut + v vt)
-  lpt += lwt[3] * k.inv_gm1;
-  lrt += lwt[3] * ke;
-  lke += lwt[3] * rt;
-  lq.r += lwt[3] * (q.u * ut + q.v * vt);
-  lq.u += lwt[3] * q.r * ut;
-  lut += lwt[3] * q.r * q.u;
-  lq.v += lwt[3] * q.r * vt;
-  lvt += lwt[3] * q.r * q.v;
-  // wt2 = rt v + r vt
-  lrt += lwt[2] * q.v;
-  lq.v += lwt[2] * rt;
-  lq.r += lwt[2] * vt;
-  lvt += lwt[2] * q.r;
-  // wt1 = rt u + r ut
-  lrt += lwt[1] * q.u;
-  lq.u += lwt[1] * rt;
-  lq.r += lwt[1] * ut;
-  lut += lwt[1] * q.r;
-  // wt0 = rt
-  lrt += lwt[0];
-  // pt = -(u px + v py + gamma p (ux + vy))
-  real lux = -lpt * k.gamma * q.p, lvy = -lpt * k.gamma * q.p;
-  real lpx = -lpt * q.u, lpy = -lpt * q.v;
-  lq.u += -lpt * px;
-  lq.v += -lpt * py;
-  lq.p += -lpt * k.gamma * (ux + vy);
-  // vt = -(u vx + v vy + py ir)
-  lq.u -= lvt * vx;
-  real lvx = -lvt * q.u;
-  lq.v -= lvt * vy;
-  lvy -= lvt * q.v;
-  lpy -= lvt * q.ir;
-  lq.ir -= lvt * py;
-  // ut = -(u ux + v uy + px ir)
-  lq.u -= lut * ux;
-  lux -= lut * q.u;
-  lq.v -= lut * uy;
-  real luy = -lut * q.v;
-  lpx -= lut * q.ir;
-  lq.ir -= lut * px;
-  // rt = -(u wx0 + r ux + v wy0 + r vy)
-  lq.u -= lrt * wx[0];
-  lwx[0] -= lrt * q.u;
-  lq.r -= lrt * (ux + vy);
-  lux -= lrt * q.r;
-  lq.v -= lrt * wy[0];
-  lwy[0] -= lrt * q.v;
-  lvy -= lrt * q.r;
-  // py, px
-  lwy[3] += k.gm1 * lpy;
-  lq.u -= k.gm1 * lpy * wy[1];
-  lwy[1] -= k.gm1 * lpy * q.u;
-  lq.v -= k.gm1 * lpy * wy[2];
-  lwy[2] -= k.gm1 * lpy * q.v;
-  lke += k.gm1 * lpy * wy[0];
-  lwy[0] += k.gm1 * lpy * ke;
-  lwx[3] += k.gm1 * lpx;
-  lq.u -= k.gm1 * lpx * wx[1];
-  lwx[1] -= k.gm1 * lpx * q.u;
-  lq.v -= k.gm1 * lpx * wx[2];
-  lwx[2] -= k.gm1 * lpx * q.v;
-  lke += k.gm1 * lpx * wx[0];
-  lwx[0] += k.gm1 * lpx * ke;
-  // vy, uy, vx, ux
-  lwy[2] += lvy * q.ir;
-  lq.v -= lvy * wy[0] * q.ir;
-  lwy[0] -= lvy * q.v * q.ir;
-  lq.ir += lvy * (wy[2] - q.v * wy[0]);
-  lwy[1] += luy * q.ir;
-  lq.u -= luy * wy[0] * q.ir;
-  lwy[0] -= luy * q.u * q.ir;
-  lq.ir += luy * (wy[1] - q.u * wy[0]);
-  lwx[2] += lvx * q.ir;
-  lq.v -= lvx * wx[0] * q.ir;
-  lwx[0] -= lvx * q.v * q.ir;
-  lq.ir += lvx * (wx[2] - q.v * wx[0]);
-  lwx[1] += lux * q.ir;
-  lq.u -= lux * wx[0] * q.ir;
-  lwx[0] -= lux * q.u * q.ir;
-  lq.ir += lux * (wx[1] - q.u * wx[0]);
-  // ke
-  lq.u += lke * q.u;
-  lq.v += lke * q.v;
+  const real u = q.u, v = q.v;
+  const real ke = real(0.5) * (u * u + v * v);
+  const real ux = wx[1] - u * wx[0], vx = wx[2] - v * wx[0];
+  const real uy = wy[1] - u * wy[0], vy = wy[2] - v * wy[0];
+  const real px = k.gm1 * (wx[3] - u * wx[1] - v * wx[2] + ke * wx[0]);
+  const real py = k.gm1 * (wy[3] - u * wy[1] - v * wy[2] + ke * wy[0]);
+  const real rt = -(wx[1] + wy[2]), dv = ux + vy;
+  const real Au = fmadd(u, ux, fmadd(v, uy, px)), Av = fmadd(u, vx, fmadd(v, vy, py));
+  const real c2 = k.gamma * q.p * q.ir, Ht = (w[3] + q.p) * q.ir;
+  const real pt = -fmadd(u, px, fmadd(v, py, c2 * dv));
+  const real wt1 = fmadd(rt, u, -Au);
+  const real wt3 = fmadd(pt, k.inv_gm1, fmadd(rt, ke, -fmadd(u, Au, v * Av)));
+  // reverse: wt_n, ft_n -> rt, Au, Av, pt
+  real l1 = lft[0] + u * lft[1] + v * lft[2], l2 = real(0), l3 = u * lft[3], lrt = real(0);
+  if (lwt) {
+    l1 += lwt[1];
+    l2 += lwt[2];
+    l3 += lwt[3];
+    lrt = lwt[0] + v * l2;
+  }
+  lrt += u * l1 + ke * l3;
+  const real lAu = -(u * lft[1] + Ht * lft[3] + l1 + u * l3), lAv = -(u * lft[2] + l2 + v * l3);
+  const real lpt = lft[1] + u * lft[3] + k.inv_gm1 * l3;
+  real lu = (wt1 - Au) * lft[1] - Av * lft[2] + (wt3 + pt) * lft[3] + rt * l1 - Au * l3;
+  real lv = wt1 * lft[2] + rt * l2 - Av * l3;
+  real lke = rt * l3;
+  const real lHt = -Au * lft[3], lc2 = -dv * lpt;
+  lw[3] += lHt * q.ir;
+  lq.p += lHt * q.ir + lc2 * k.gamma * q.ir;
+  lq.ir += lHt * (w[3] + q.p) + lc2 * k.gamma * q.p;
+  const real ldv = -c2 * lpt;
+  const real gpx = k.gm1 * (lAu - u * lpt), gpy = k.gm1 * (lAv - v * lpt);  // gm1 times those of px, py
+  const real lux = u * lAu + ldv, luy = v * lAu, lvx = u * lAv, lvy = v * lAv + ldv;
+  lu += ux * lAu + vx * lAv - px * lpt - (wx[1] * gpx + wy[1] * gpy) - (wx[0] * lux + wy[0] * luy);
+  lv += uy * lAu + vy * lAv - py * lpt - (wx[2] * gpx + wy[2] * gpy) - (wx[0] * lvx + wy[0] * lvy);
+  lke += wx[0] * gpx + wy[0] * gpy;
+  lwx[0] += ke * gpx - u * lux - v * lvx;
+  lwx[1] += lux - u * gpx - lrt;
+  lwx[2] += lvx - v * gpx;
+  lwx[3] += gpx;
+  lwy[0] += ke * gpy - u * luy - v * lvy;
+  lwy[1] += luy - u * gpy;
+  lwy[2] += lvy - v * gpy - lrt;
+  lwy[3] += gpy;
+  lq.u += lu + lke * u;
+  lq.v += lv + lke * v;
 }
 
+// lF: adjoint of the flux, null where the flux itself is not used (the second stage).
 template <class real>
 DFW_HD void lf_flux_adj(const real* wl, const real* wlx, const real* wly, const real* wr, const real* wrx,
                         const real* wry, const Prim<real>& ql, const Prim<real>& qr, const Coef<real>& k,
@@ -537,208 +469,163 @@ DFW_HD void lf_flux_adj(const real* wl, const real* wlx, const real* wly, const 
   euler_time_derivs(wl, ql, wlx, wly, k, wtl, ftl);
   euler_time_derivs(wr, qr, wrx, wry, k, wtr, ftr);
   real lhs = real(0);
-  real lwtl[4], lwtr[4], lftl[4], lftr[4];
-  real lFl[4], lFr[4];
+  real lwtl[4], lwtr[4], lfth[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    lhs -= lF[c] * (wr[c] - wl[c]) + lFt[c] * (wtr[c] - wtl[c]);
-    lwr[c] -= hs * lF[c];
-    lwl[c] += hs * lF[c];
-    lFl[c] = real(0.5) * lF[c];
-    lFr[c] = real(0.5) * lF[c];
+    lhs -= lFt[c] * (wtr[c] - wtl[c]);
     lwtr[c] = -hs * lFt[c];
     lwtl[c] = hs * lFt[c];
-    lftl[c] = real(0.5) * lFt[c];
-    lftr[c] = real(0.5) * lFt[c];
+    lfth[c] = real(0.5) * lFt[c];
   }
-  real ls = real(0.5) * lhs;
+  if (lF) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      lhs -= lF[c] * (wr[c] - wl[c]);
+      lwr[c] -= hs * lF[c];
+      lwl[c] += hs * lF[c];
+    }
+    // F = (w1, w1 u + p, w2 u, u (w3 + p)) on each side
+    const real h[4] = {real(0.5) * lF[0], real(0.5) * lF[1], real(0.5) * lF[2], real(0.5) * lF[3]};
+    lwl[1] += h[0] + h[1] * ql.u;
+    lql.u += h[1] * wl[1] + h[2] * wl[2] + h[3] * (wl[3] + ql.p);
+    lql.p += h[1] + h[3] * ql.u;
+    lwl[2] += h[2] * ql.u;
+    lwl[3] += h[3] * ql.u;
+    lwr[1] += h[0] + h[1] * qr.u;
+    lqr.u += h[1] * wr[1] + h[2] * wr[2] + h[3] * (wr[3] + qr.p);
+    lqr.p += h[1] + h[3] * qr.u;
+    lwr[2] += h[2] * qr.u;
+    lwr[3] += h[3] * qr.u;
+  }
+  const real ls = real(0.5) * lhs;
   if (left) {
-    lql.u += sgn(ql.u) * ls;
+    lql.u += signed_by(ls, ql.u);
     lql.c += ls;
   } else {
-    lqr.u += sgn(qr.u) * ls;
+    lqr.u += signed_by(ls, qr.u);
     lqr.c += ls;
   }
-  // F = (w1, w1 u + p, w2 u, u (w3 + p)) on each side
-  lwl[1] += lFl[0] + lFl[1] * ql.u;
-  lql.u += lFl[1] * wl[1] + lFl[2] * wl[2] + lFl[3] * (wl[3] + ql.p);
-  lql.p += lFl[1] + lFl[3] * ql.u;
-  lwl[2] += lFl[2] * ql.u;
-  lwl[3] += lFl[3] * ql.u;
-  lwr[1] += lFr[0] + lFr[1] * qr.u;
-  lqr.u += lFr[1] * wr[1] + lFr[2] * wr[2] + lFr[3] * (wr[3] + qr.p);
-  lqr.p += lFr[1] + lFr[3] * qr.u;
-  lwr[2] += lFr[2] * qr.u;
-  lwr[3] += lFr[3] * qr.u;
-  euler_time_derivs_adj(wl, ql, wlx, wly, k, lwtl, lftl, lwl, lql, lwlx, lwly);
-  euler_time_derivs_adj(wr, qr, wrx, wry, k, lwtr, lftr, lwr, lqr, lwrx, lwry);
+  euler_time_derivs_adj(wl, ql, wlx, wly, k, lwtl, lfth, lwl, lql, lwlx, lwly);
+  euler_time_derivs_adj(wr, qr, wrx, wry, k, lwtr, lfth, lwr, lqr, lwrx, lwry);
 }
 
 // ------------------------------------------------------------------------------------------------
 // Gas-kinetic flux.
 // ------------------------------------------------------------------------------------------------
+// The flux goes through derivatives of moments (gks_side, add_second_moments of dfw_math.hpp); its
+// reverse goes back through them.  About 12 000 flops per Gauss point went into the reverse of the
+// moments folded with micro-slopes; this one takes about 1 500.
+// ------------------------------------------------------------------------------------------------
 template <class real>
-struct MomAdj {
-  real mu[7], mv[6], mx[3];
-  DFW_HD void zero() {
-#pragma unroll
-    for (int i = 0; i < 7; ++i) mu[i] = real(0);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) mv[i] = real(0);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) mx[i] = real(0);
-  }
+struct GasAdj {  // adjoints of a Maxwellian's mean U, V, of h = p/rho, X = <v^2 + xi^2> and mu[0..4]
+  real U, V, h, X, mu[5];
 };
 
 template <class real>
-DFW_HD void mom_adj(const Mom<real>& M, int a, int b, int c, real l, MomAdj<real>& lM) {
-  lM.mu[a] += l * M.mv[b] * M.mx[c];
-  lM.mv[b] += l * M.mu[a] * M.mx[c];
-  lM.mx[c] += l * M.mu[a] * M.mv[b];
-}
-
-// <(s.psi) u^a v^b xi^2c>: adjoint into the slope and the moments
-template <class real>
-DFW_HD void mom_s_adj(const Mom<real>& M, const real* s, int a, int b, int c, real l, real* ls, MomAdj<real>& lM) {
-  ls[0] += l * mom(M, a, b, c);
-  ls[1] += l * mom(M, a + 1, b, c);
-  ls[2] += l * mom(M, a, b + 1, c);
-  ls[3] += l * real(0.5) * (mom(M, a + 2, b, c) + mom(M, a, b + 2, c) + mom(M, a, b, c + 1));
-  mom_adj(M, a, b, c, l * s[0], lM);
-  mom_adj(M, a + 1, b, c, l * s[1], lM);
-  mom_adj(M, a, b + 1, c, l * s[2], lM);
-  const real h3 = real(0.5) * s[3] * l;
-  mom_adj(M, a + 2, b, c, h3, lM);
-  mom_adj(M, a, b + 2, c, h3, lM);
-  mom_adj(M, a, b, c + 1, h3, lM);
+DFW_HD void gas_slope_adj(const real* w, real U, real V, real h, real ke, const GasSlope<real>& l,
+                          const Coef<real>& k, real* lw, GasAdj<real>& g, real& lke) {
+  const real lP = k.gm1 * l.e;
+  lw[0] += l.r - U * l.a - V * l.b - h * l.e + ke * lP;
+  lw[1] += l.a - U * lP;
+  lw[2] += l.b - V * lP;
+  lw[3] += lP;
+  g.U -= l.a * w[0] + lP * w[1];
+  g.V -= l.b * w[0] + lP * w[2];
+  g.h -= l.e * w[0];
+  lke += lP * w[0];
 }
 
 template <class real>
-DFW_HD void mom_s_psi_adj(const Mom<real>& M, const real* s, int a, int b, const real* l, real* ls, MomAdj<real>& lM) {
-  mom_s_adj(M, s, a, b, 0, l[0], ls, lM);
-  mom_s_adj(M, s, a + 1, b, 0, l[1], ls, lM);
-  mom_s_adj(M, s, a, b + 1, 0, l[2], ls, lM);
-  const real h = real(0.5) * l[3];
-  mom_s_adj(M, s, a + 2, b, 0, h, ls, lM);
-  mom_s_adj(M, s, a, b + 2, 0, h, ls, lM);
-  mom_s_adj(M, s, a, b, 1, h, ls, lM);
+DFW_HD void slope_d1_adj(const GasSlope<real>& s, const real* mu, real l, GasSlope<real>& ls, GasAdj<real>& g) {
+  ls.r += l * mu[1];
+  ls.a += l * mu[0];
+  g.mu[1] += l * s.r;
+  g.mu[0] += l * s.a;
 }
-
 template <class real>
-DFW_HD void mom_psi_adj(const Mom<real>& M, int a, int b, const real* l, MomAdj<real>& lM) {
-  mom_adj(M, a, b, 0, l[0], lM);
-  mom_adj(M, a + 1, b, 0, l[1], lM);
-  mom_adj(M, a, b + 1, 0, l[2], lM);
-  const real h = real(0.5) * l[3];
-  mom_adj(M, a + 2, b, 0, h, lM);
-  mom_adj(M, a, b + 2, 0, h, lM);
-  mom_adj(M, a, b, 1, h, lM);
+DFW_HD void slope_d2_adj(const GasSlope<real>& s, const real* mu, real l, GasSlope<real>& ls, GasAdj<real>& g) {
+  const real l2 = real(2) * l;
+  ls.r += l * mu[2];
+  ls.a += l2 * mu[1];
+  ls.e += l * mu[0];
+  g.mu[2] += l * s.r;
+  g.mu[1] += l2 * s.a;
+  g.mu[0] += l * s.e;
 }
-
-// Reverse of maxwell_moments: -> adjoints of U, V, lambda.
 template <class real>
-DFW_HD void maxwell_moments_adj(const Mom<real>& M, int side, const Coef<real>& k, MomAdj<real> lM, real& lU, real& lV,
-                                real& llam) {
-  const real U = M.U, V = M.V, lam = M.lam;
-  const real h = real(0.5) / lam;
-  real lh = lM.mx[1] * k.K + lM.mx[2] * real(2) * k.K * (k.K + real(2)) * h;
-#pragma unroll
-  for (int n = 3; n >= 0; --n) {  // mv[n+2] = V mv[n+1] + (n+1) h mv[n]
-    const real l = lM.mv[n + 2];
-    lV += l * M.mv[n + 1];
-    lM.mv[n + 1] += l * V;
-    lh += l * real(n + 1) * M.mv[n];
-    lM.mv[n] += l * real(n + 1) * h;
-  }
-  lV += lM.mv[1];
-#pragma unroll
-  for (int n = 4; n >= 0; --n) {
-    const real l = lM.mu[n + 2];
-    lU += l * M.mu[n + 1];
-    lM.mu[n + 1] += l * U;
-    lh += l * real(n + 1) * M.mu[n];
-    lM.mu[n] += l * real(n + 1) * h;
-  }
-  if (side == 0) {
-    lU += lM.mu[1];
-  } else {
-    const real inv_sqrt_pi = real(0.56418958354775628695);
-    const real sg = side > 0 ? real(1) : real(-1);
-    real sl = sqrt(lam);
-    real ex = exp(-lam * U * U);
-    real g = real(0.5) * ex * inv_sqrt_pi / sl;
-    // mu1 = U mu0 +- g
-    lU += lM.mu[1] * M.mu[0];
-    real lmu0 = lM.mu[0] + lM.mu[1] * U;
-    real lg = sg * lM.mu[1];
-    // mu0 = erfc(-sg sl U)/2: d/dz erfc(z)/2 = -exp(-z^2)/sqrt(pi), z = -sg sl U
-    real dmu0 = -inv_sqrt_pi * ex;
-    lU += lmu0 * dmu0 * (-sg * sl);
-    real lsl = lmu0 * dmu0 * (-sg * U);
-    // g = exp(-lam U^2) / (2 sqrt(pi) sl)
-    lU += lg * g * (real(-2) * lam * U);
-    llam += lg * g * (-U * U);
-    lsl += -lg * g / sl;
-    llam += lsl * real(0.5) / sl;
-  }
-  llam += -lh * real(0.5) / (lam * lam);
+DFW_HD void slope_d3_adj(const GasSlope<real>& s, const real* mu, real l, GasSlope<real>& ls, GasAdj<real>& g) {
+  const real l3 = real(3) * l;
+  ls.r += l * mu[3];
+  ls.a += l3 * mu[2];
+  ls.e += l3 * mu[1];
+  g.mu[3] += l * s.r;
+  g.mu[2] += l3 * s.a;
+  g.mu[1] += l3 * s.e;
 }
-
 template <class real>
-DFW_HD void micro_slope_adj(const real* g, real U, real V, real lam, const Coef<real>& k, const real* ls_in, real* lg,
-                            real& lU, real& lV, real& llam) {
-  const real K2 = k.K2;
-  const real ilam = real(1) / lam;
-  real B = U * U + V * V + K2 * real(0.5) * ilam;
-  real R4 = real(2) * g[3] - B * g[0];
-  real R3 = g[2] - V * g[0];
-  real R2 = g[1] - U * g[0];
-  real kap = k.k4K2 * (lam * lam);
-  real Z = R4 - real(2) * U * R2 - real(2) * V * R3;
-  real s3 = kap * Z;
-  real s2 = real(2) * lam * R3 - V * s3;
-  real s1 = real(2) * lam * R2 - U * s3;
-  // s0 = g0 - U s1 - V s2 - s3 B / 2
-  real ls1 = ls_in[1] - U * ls_in[0];
-  real ls2 = ls_in[2] - V * ls_in[0];
-  real ls3 = ls_in[3] - real(0.5) * B * ls_in[0];
-  lg[0] += ls_in[0];
-  lU -= ls_in[0] * s1;
-  lV -= ls_in[0] * s2;
-  real lB = -real(0.5) * s3 * ls_in[0];
-  // s1 = 2 lam R2 - U s3 ; s2 = 2 lam R3 - V s3
-  llam += real(2) * R2 * ls1 + real(2) * R3 * ls2;
-  real lR2 = real(2) * lam * ls1, lR3 = real(2) * lam * ls2;
-  lU -= s3 * ls1;
-  lV -= s3 * ls2;
-  ls3 -= U * ls1 + V * ls2;
-  // s3 = kap Z
-  llam += ls3 * Z * real(2) * lam * k.k4K2;
-  real lZ = ls3 * kap;
-  real lR4 = lZ;
-  lU -= real(2) * R2 * lZ;
-  lR2 -= real(2) * U * lZ;
-  lV -= real(2) * R3 * lZ;
-  lR3 -= real(2) * V * lZ;
-  lg[1] += lR2;
-  lU -= g[0] * lR2;
-  lg[0] -= U * lR2;
-  lg[2] += lR3;
-  lV -= g[0] * lR3;
-  lg[0] -= V * lR3;
-  lg[3] += real(2) * lR4;
-  lB -= g[0] * lR4;
-  lg[0] -= B * lR4;
-  lU += real(2) * U * lB;
-  lV += real(2) * V * lB;
-  llam += -K2 * real(0.5) * (ilam * ilam) * lB;
+DFW_HD void slope_d4_adj(const GasSlope<real>& s, const real* mu, real l, GasSlope<real>& ls, GasAdj<real>& g) {
+  const real l4 = real(4) * l, l6 = real(6) * l;
+  ls.r += l * mu[4];
+  ls.a += l4 * mu[3];
+  ls.e += l6 * mu[2];
+  g.mu[4] += l * s.r;
+  g.mu[3] += l4 * s.a;
+  g.mu[2] += l6 * s.e;
 }
 
-// Adjoint of gks_flux (lF may be null when the flux itself was not requested), in two halves.  The first recomputes the flux and reverses its time
-// coefficients and the equilibrium-state part, down to the adjoints of the half-space sums
-// (Wc, Wcn, Wct, Flr, Malr) and the pressure-jump term of tau; the second reverses the two
-// half-space sides.  A caller short of registers can keep the handover in memory between them;
-// gks_flux_adj runs both in turn.
+// Reverse of add_second_moments for the adjoint l of M (energy component doubled); the adjoint of d1 is
+// added to ld1.
+template <class real>
+DFW_HD void second_moments_adj(const GasSlope<real>& sx, const GasSlope<real>& sy, const real* mu, real V, real h,
+                               real X, real d1, const Coef<real>& k, const real* l, GasSlope<real>& lx,
+                               GasSlope<real>& ly, GasAdj<real>& g, real& ld1) {
+  const real K1 = k.K + real(1), K3 = k.K + real(3);
+  const real d2 = slope_d2(sx, mu), t2 = slope_d2(sy, mu), t3 = slope_d3(sy, mu);
+  const real vb = real(2) * V * sy.b, Z = fmadd(real(2), h, X), Vl3 = V * l[3];
+  const real mz = fmadd(K3, sy.e, vb);
+  slope_d2_adj(sx, mu, fmadd(X, l[3], fmadd(V, l[2], l[0])), lx, g);
+  slope_d3_adj(sx, mu, l[1], lx, g);
+  slope_d4_adj(sx, mu, l[3], lx, g);
+  slope_d2_adj(sy, mu, V * l[1], ly, g);
+  slope_d3_adj(sy, mu, Vl3, ly, g);
+  ld1 += fmadd(Z, Vl3, fmadd(fmadd(V, V, h), l[2], V * l[0]));
+  g.mu[1] += sy.b * l[0] + (vb + sy.e) * l[2] + (V * mz + sy.b * Z) * l[3];
+  g.mu[2] += sy.b * l[1] + sx.b * l[2] + fmadd(real(2) * V, sx.b, K1 * sx.e) * l[3];
+  g.mu[3] += sy.b * l[3];
+  const real lvb = mu[1] * (l[2] + Vl3);
+  ly.b += mu[1] * l[0] + mu[2] * l[1] + fmadd(Z, mu[1], mu[3]) * l[3] + real(2) * V * lvb;
+  lx.b += mu[2] * fmadd(real(2), Vl3, l[2]);
+  lx.e += K1 * mu[2] * l[3];
+  ly.e += mu[1] * fmadd(K3, Vl3, l[2]);
+  g.V += d1 * l[0] + t2 * l[1] + (d2 + real(2) * V * d1) * l[2] + real(2) * sy.b * lvb +
+         (real(2) * sx.b * mu[2] + Z * d1 + mu[1] * mz + t3) * l[3];
+  const real lZ = l[3] * fmadd(V, d1, sy.b * mu[1]);
+  g.X += fmadd(d2, l[3], lZ);
+  g.h += fmadd(d1, l[2], real(2) * lZ);
+}
+
+// mu_2..mu_4 by the recursion mu_{n+2} = U mu_{n+1} + (n + 1) h mu_n, reversed into U, h, mu_0, mu_1.
+template <class real>
+DFW_HD void moments_adj(const real* mu, real U, real h, GasAdj<real>& g) {
+  g.U += g.mu[4] * mu[3];
+  g.mu[3] += g.mu[4] * U;
+  g.h += real(3) * g.mu[4] * mu[2];
+  g.mu[2] += real(3) * g.mu[4] * h;
+  g.U += g.mu[3] * mu[2];
+  g.mu[2] += g.mu[3] * U;
+  g.h += real(2) * g.mu[3] * mu[1];
+  g.mu[1] += real(2) * g.mu[3] * h;
+  g.U += g.mu[2] * mu[1];
+  g.mu[1] += g.mu[2] * U;
+  g.h += g.mu[2] * mu[0];
+  g.mu[0] += g.mu[2] * h;
+}
+
+// Adjoint of the GKS flux (lF null where the flux itself is not used), in two halves.  The first
+// recomputes the flux and reverses its time coefficients and the equilibrium-state part, down to the
+// adjoints of the half-space sums (Wc, Wcn, Wct, Flr, Malr, with doubled energy components) and the
+// pressure-jump term of tau; the second reverses the two half-space sides.  A caller short of
+// registers can keep the handover in memory between them; gks_flux_adj runs both in turn.
 template <class real>
 struct GksEqAdj {
   real lWc[4], lWcn[4], lWct[4], lFlr[4], lMalr[4];
@@ -752,174 +639,178 @@ DFW_HD void gks_flux_adj_eq(const real* wln, const real* wlt, const real* wrn, c
   // ---- forward recompute
   real Wc[4] = {0, 0, 0, 0}, Wcn[4] = {0, 0, 0, 0}, Wct[4] = {0, 0, 0, 0};
   real Flr[4] = {0, 0, 0, 0}, Malr[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const real* wn = side == 0 ? wln : wrn;
-    const real* wt = side == 0 ? wlt : wrt;
-    const Prim<real>& q = side == 0 ? ql : qr;
-    real lam = real(0.5) * q.r / q.p;
-    Mom<real> M;
-    maxwell_moments(q.u, q.v, lam, side == 0 ? 1 : -1, k, M);
-    real g[4], a[4], b[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) g[c] = wn[c] * q.ir;
-    micro_slope(g, q.u, q.v, lam, real(0.5) / lam, k, a);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) g[c] = wt[c] * q.ir;
-    micro_slope(g, q.u, q.v, lam, real(0.5) / lam, k, b);
-    real t0[4], t1[4], t2[4];
-    mom_psi(M, 0, 0, t0);
-    mom_s_psi(M, a, 0, 0, t1);
-    mom_s_psi(M, b, 0, 0, t2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      Wc[c] += q.r * t0[c];
-      Wcn[c] += q.r * t1[c];
-      Wct[c] += q.r * t2[c];
-    }
-    mom_psi(M, 1, 0, t0);
-    mom_s_psi(M, a, 2, 0, t1);
-    mom_s_psi(M, b, 1, 1, t2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      Flr[c] += q.r * t0[c];
-      Malr[c] += q.r * (t1[c] + t2[c]);
-    }
-  }
-  real irc = real(1) / Wc[0];
-  real Uc = Wc[1] * irc, Vc = Wc[2] * irc;
-  real pc = k.gm1 * (Wc[3] - real(0.5) * (Wc[1] * Uc + Wc[2] * Vc));
-  real lamc = real(0.5) * Wc[0] / pc;
-  Mom<real> Mc;
-  maxwell_moments(Uc, Vc, lamc, 0, k, Mc);
-  real gn[4], gt[4], ac[4], bc[4], Ac[4], gA[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    gn[c] = Wcn[c] * irc;
-    gt[c] = Wct[c] * irc;
-  }
-  micro_slope(gn, Uc, Vc, lamc, real(0.5) / lamc, k, ac);
-  micro_slope(gt, Uc, Vc, lamc, real(0.5) / lamc, k, bc);
-  real y1[4], y2[4];
-  mom_s_psi(Mc, ac, 1, 0, y1);
-  mom_s_psi(Mc, bc, 0, 1, y2);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) gA[c] = -(y1[c] + y2[c]);
-  micro_slope(gA, Uc, Vc, lamc, real(0.5) / lamc, k, Ac);
-  real fc[4], x1[4], x2[4], xA[4];
-  mom_psi(Mc, 1, 0, fc);
-  mom_s_psi(Mc, ac, 2, 0, x1);
-  mom_s_psi(Mc, bc, 1, 1, x2);
-  mom_s_psi(Mc, Ac, 1, 0, xA);
-  real Fc[4], Mac[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    Fc[c] = Wc[0] * fc[c];
-    Mac[c] = Wc[0] * (x1[c] + x2[c]);
-  }
-  const real pq = (ql.p - qr.p) / (ql.p + qr.p);
-  real tau = k.c1 * dt + k.c2 * fabs(pq) * dt;
-  real E2 = exp(-real(0.5) * dt / tau);
-  real E1 = E2 * E2;
-  real om = real(1) - E2;
-  real idt = real(1) / dt;
-  real ct1 = real(4) * tau * om * om * idt * idt;
-  real ct2 = real(4) * (tau * dt * E2 * om - tau * tau * om * om) * idt * idt;
-  real z = real(3) - real(4) * E2 + E1;
-  real cf1 = real(1) - tau * idt * z;
-  real cf2 = tau * tau * idt * z + tau * (E1 - real(2) * E2);
-  // ---- reverse: time coefficients
-  real lFc[4], lMac[4], lMAc[4];
-  real* lFlr = e.lFlr;
-  real* lMalr = e.lMalr;
-  e.lpl = e.lpr = real(0);
+  real s2h, is;
+  real h = ql.p * ql.ir;
+  sqrt_inv(real(2) * h, s2h, is);
+  gks_side<1>(ql, h, s2h, is, wln, wlt, k, Wc, Wcn, Wct, Flr, Malr);
+  h = qr.p * qr.ir;
+  sqrt_inv(real(2) * h, s2h, is);
+  gks_side<-1>(qr, h, s2h, is, wrn, wrt, k, Wc, Wcn, Wct, Flr, Malr);
+  Wc[3] *= real(0.5);
+  Wcn[3] *= real(0.5);
+  Wct[3] *= real(0.5);
+  Prim<real> c;
+  c.r = Wc[0];
+  c.ir = rcp_any(Wc[0]);
+  c.u = Wc[1] * c.ir;
+  c.v = Wc[2] * c.ir;
+  c.p = k.gm1 * (Wc[3] - real(0.5) * (Wc[1] * c.u + Wc[2] * c.v));
+  h = c.p * c.ir;
+  const real U = c.u, V = c.v, K1 = k.K + real(1);
+  real mu[5];
+  mu[0] = real(1);
+  mu[1] = U;
+  mu[2] = fmadd(U, U, h);
+  mu[3] = fmadd(U, mu[2], real(2) * h * U);
+  mu[4] = fmadd(U, mu[3], real(3) * h * mu[2]);
+  const real ke = real(0.5) * (U * U + V * V), X = fmadd(V, V, K1 * h);
+  const GasSlope<real> sx = gas_slope(Wcn, U, V, h, ke, k), sy = gas_slope(Wct, U, V, h, ke, k);
+  const real d1 = slope_d1(sy, mu);
+  real Mac[4] = {0, 0, 0, 0};
+  add_second_moments(sx, sy, mu, V, h, X, d1, k, Mac);
+  const real Fc[4] = {Wc[1], fmadd(Wc[1], U, c.p), Wc[2] * U, U * (Wc[3] + c.p)};
+  // ---- time coefficients, forward and reverse
+  const real isum = rcp_any(ql.p + qr.p), pq = (ql.p - qr.p) * isum;
+  const real x = k.c1 + k.c2 * fabs(pq), ix = rcp_any(x), idt = rcp_any(dt);
+  const real E2 = exp(real(-0.5) * ix), om = real(1) - E2, xo = x * om;
+  const real ct1 = (real(4) * xo * om) * idt, ct2 = real(4) * xo * (E2 - xo);
+  const real z = om * (real(3) - E2), ee = E2 * (E2 - real(2));
+  const real cf1 = real(1) - x * z, cf2 = dt * (x * fmadd(x, z, ee));
+  real lFc[4], lMac[4];
   real lct1 = real(0), lct2 = real(0), lcf1 = real(0), lcf2 = real(0);
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const real MA = Wc[0] * xA[c];
-    (void)MA;
-    lct1 += lFt[c] * (Fc[c] - Flr[c]);
-    lct2 += lFt[c] * (Mac[c] - Malr[c]);
-    lFc[c] = ct1 * lFt[c];
-    lFlr[c] = -ct1 * lFt[c];
-    lMac[c] = ct2 * lFt[c];
-    lMalr[c] = -ct2 * lFt[c];
-    lMAc[c] = lFt[c];
+  for (int i = 0; i < 4; ++i) {
+    const real half = i == 3 ? real(0.5) : real(1);
+    const real dM = half * (Mac[i] - Malr[i]), dF = Fc[i] - half * Flr[i];
+    real ldF = ct1 * lFt[i], ldM = ct2 * lFt[i], lflr = real(0);
+    lct1 += lFt[i] * dF;
+    lct2 += lFt[i] * dM;
     if (lF) {
-      lcf1 += lF[c] * (Fc[c] - Flr[c]);
-      lcf2 += lF[c] * (Mac[c] - Malr[c]);
-      lFc[c] += cf1 * lF[c];
-      lFlr[c] += (real(1) - cf1) * lF[c];
-      lMac[c] += cf2 * lF[c];
-      lMalr[c] -= cf2 * lF[c];
+      lcf1 += lF[i] * dF;
+      lcf2 += lF[i] * dM;
+      ldF += cf1 * lF[i];
+      ldM += cf2 * lF[i];
+      lflr = lF[i];
     }
+    lFc[i] = ldF;
+    lMac[i] = half * ldM;
+    e.lFlr[i] = half * (lflr - ldF);
+    e.lMalr[i] = -lMac[i];
   }
-  if (tau > real(0)) {
-    real dE2 = E2 * real(0.5) * dt / (tau * tau);
-    real dct1 = real(4) * idt * idt * (om * om - real(2) * tau * om * dE2);
-    real dct2 = real(4) * idt * idt *
-                (dt * E2 * om + tau * dt * (dE2 * om - E2 * dE2) - real(2) * tau * om * om + real(2) * tau * tau * om * dE2);
-    real dz = (real(-4) + real(2) * E2) * dE2;
-    real dcf1 = -idt * (z + tau * dz);
-    real dcf2 = real(2) * tau * idt * z + tau * tau * idt * dz + (E1 - real(2) * E2) + tau * (real(2) * E2 - real(2)) * dE2;
-    real ltau = lct1 * dct1 + lct2 * dct2 + lcf1 * dcf1 + lcf2 * dcf2;
-    real lpq = ltau * k.c2 * dt * sgn(pq);
-    real isum = real(1) / (ql.p + qr.p);
-    e.lpl = lpq * (real(1) - pq) * isum;
-    e.lpr = lpq * (real(-1) - pq) * isum;
+  e.lpl = e.lpr = real(0);
+  if (x > real(0)) {
+    const real dE2 = real(0.5) * E2 * (ix * ix), dxo = om - x * dE2;
+    const real dct1 = real(4) * idt * (dxo * om - xo * dE2);
+    const real dct2 = real(4) * (dxo * (E2 - xo) + xo * (dE2 - dxo));
+    const real dz = (real(2) * E2 - real(4)) * dE2;
+    const real dcf1 = -(z + x * dz), dcf2 = dt * (real(2) * x * z + ee + x * (x * dz - real(2) * om * dE2));
+    const real lx = lct1 * dct1 + lct2 * dct2 + lcf1 * dcf1 + lcf2 * dcf2;
+    const real lpq = signed_by(lx * k.c2, pq) * isum;
+    e.lpl = lpq * (real(1) - pq);
+    e.lpr = lpq * (real(-1) - pq);
   }
-  // ---- reverse: equilibrium-state fluxes
-  MomAdj<real> lMc;
-  lMc.zero();
-  real* lWc = e.lWc;
-  real* lWcn = e.lWcn;
-  real* lWct = e.lWct;
+  // ---- equilibrium state: Fc, MA_c and Ma_c -> Wc and its derivatives
 #pragma unroll
-  for (int c = 0; c < 4; ++c) lWc[c] = lWcn[c] = lWct[c] = real(0);
-  real lac[4] = {0, 0, 0, 0}, lbc[4] = {0, 0, 0, 0}, lAc[4] = {0, 0, 0, 0};
-  real lx[4], lfc[4], lxA[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    lWc[0] += lFc[c] * fc[c] + lMac[c] * (x1[c] + x2[c]) + lMAc[c] * xA[c];
-    lfc[c] = Wc[0] * lFc[c];
-    lx[c] = Wc[0] * lMac[c];
-    lxA[c] = Wc[0] * lMAc[c];
-  }
-  mom_psi_adj(Mc, 1, 0, lfc, lMc);
-  mom_s_psi_adj(Mc, ac, 2, 0, lx, lac, lMc);
-  mom_s_psi_adj(Mc, bc, 1, 1, lx, lbc, lMc);
-  mom_s_psi_adj(Mc, Ac, 1, 0, lxA, lAc, lMc);
-  real lUc = real(0), lVc = real(0), llamc = real(0);
-  real lgA[4] = {0, 0, 0, 0};
-  micro_slope_adj(gA, Uc, Vc, lamc, k, lAc, lgA, lUc, lVc, llamc);
-  real ly[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) ly[c] = -lgA[c];
-  mom_s_psi_adj(Mc, ac, 1, 0, ly, lac, lMc);
-  mom_s_psi_adj(Mc, bc, 0, 1, ly, lbc, lMc);
-  real lgn[4] = {0, 0, 0, 0}, lgt[4] = {0, 0, 0, 0};
-  micro_slope_adj(gn, Uc, Vc, lamc, k, lac, lgn, lUc, lVc, llamc);
-  micro_slope_adj(gt, Uc, Vc, lamc, k, lbc, lgt, lUc, lVc, llamc);
-  real lirc = real(0);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    lWcn[c] += lgn[c] * irc;
-    lWct[c] += lgt[c] * irc;
-    lirc += lgn[c] * Wcn[c] + lgt[c] * Wct[c];
-  }
-  maxwell_moments_adj(Mc, 0, k, lMc, lUc, lVc, llamc);
-  // lamc = Wc0 / (2 pc), pc = gm1 (Wc3 - (Wc1 Uc + Wc2 Vc)/2), Uc = Wc1 irc, Vc = Wc2 irc, irc = 1/Wc0
-  lWc[0] += llamc * real(0.5) / pc;
-  real lpc = -llamc * lamc / pc;
-  lWc[3] += lpc * k.gm1;
-  lWc[1] += -lpc * k.gm1 * real(0.5) * Uc;
-  lWc[2] += -lpc * k.gm1 * real(0.5) * Vc;
-  lUc += -lpc * k.gm1 * real(0.5) * Wc[1];
-  lVc += -lpc * k.gm1 * real(0.5) * Wc[2];
-  lWc[1] += lUc * irc;
-  lWc[2] += lVc * irc;
-  lirc += lUc * Wc[1] + lVc * Wc[2];
-  lWc[0] += -lirc * irc * irc;
+  for (int i = 0; i < 4; ++i) e.lWc[i] = e.lWcn[i] = e.lWct[i] = real(0);
+  PrimAdj<real> lq;
+  lq.zero();
+  e.lWc[1] += lFc[0] + lFc[1] * U;
+  e.lWc[2] += lFc[2] * U;
+  e.lWc[3] += lFc[3] * U;
+  lq.u += lFc[1] * Wc[1] + lFc[2] * Wc[2] + lFc[3] * (Wc[3] + c.p);
+  lq.p += lFc[1] + lFc[3] * U;
+  euler_time_derivs_adj(Wc, c, Wcn, Wct, k, (const real*)nullptr, lFt, e.lWc, lq, e.lWcn, e.lWct);
+  GasSlope<real> lx{0, 0, 0, 0}, ly{0, 0, 0, 0};
+  GasAdj<real> g{};
+  real ld1 = real(0), lke = real(0);
+  second_moments_adj(sx, sy, mu, V, h, X, d1, k, lMac, lx, ly, g, ld1);
+  slope_d1_adj(sy, mu, ld1, ly, g);
+  gas_slope_adj(Wcn, U, V, h, ke, lx, k, e.lWcn, g, lke);
+  gas_slope_adj(Wct, U, V, h, ke, ly, k, e.lWct, g, lke);
+  moments_adj(mu, U, h, g);
+  lq.u += g.U + g.mu[1] + lke * U;
+  lq.v += g.V + real(2) * V * g.X + lke * V;
+  const real lh = fmadd(K1, g.X, g.h);
+  prim_adj(Wc, c, k, lq, lq.p + lh * c.ir, lq.ir + lh * c.p, e.lWc);
+  e.lWc[3] *= real(0.5);
+  e.lWcn[3] *= real(0.5);
+  e.lWct[3] *= real(0.5);
+}
+
+// Reverse of the first moments of one direction, M = [d0, d1, V d0 + b mu0, X d0 + mu0 (2 V b + K1 e) + D_2] with
+// the half-space d0, d1 (boundary term G, zi = U/(2h)), for the adjoint l of M; ld1 adds to d1's.  lG, lzi
+// accumulate.
+template <class real>
+DFW_HD void first_moments_adj(const GasSlope<real>& s, const real* mu, real V, real X, real G, real zi,
+                              const Coef<real>& k, const real* l, real ld1, GasSlope<real>& ls, GasAdj<real>& g,
+                              real& lG, real& lzi) {
+  const real K1 = k.K + real(1);
+  const real az = fmadd(-zi, s.e, s.a), d0 = fmadd(s.r, mu[0], G * az);
+  const real ld0 = fmadd(X, l[3], fmadd(V, l[2], l[0])), lq = mu[0] * l[3];
+  ld1 += l[1];
+  g.V += d0 * l[2] + real(2) * s.b * lq;
+  g.X += d0 * l[3];
+  g.mu[0] += s.b * l[2] + fmadd(real(2) * V, s.b, K1 * s.e) * l[3] + ld0 * s.r;
+  ls.b += mu[0] * l[2] + real(2) * V * lq;
+  const real lGa = ld0 * G;
+  ls.r += ld0 * mu[0];
+  ls.a += lGa;
+  ls.e += K1 * lq - lGa * zi + real(0.5) * ld1 * G;
+  lG += ld0 * az + real(0.5) * ld1 * s.e;
+  lzi -= lGa * s.e;
+  slope_d1_adj(s, mu, ld1, ls, g);
+  slope_d2_adj(s, mu, l[3], ls, g);
+}
+
+// One half-space side.
+template <int SG, class real>
+DFW_HD void gks_side_adj(const Prim<real>& q, const real* wn, const real* wt, const Coef<real>& k,
+                         const GksEqAdj<real>& e, real* lwn, real* lwt, PrimAdj<real>& lq) {
+  // ---- forward recompute
+  const real inv_sqrt_pi = real(SG * 0.56418958354775628695);
+  const real U = q.u, V = q.v, h = q.p * q.ir, K1 = k.K + real(1);
+  real s2h, is, mu[5];
+  sqrt_inv(real(2) * h, s2h, is);
+  const real z = is * U, ex = exp(-(z * z));
+  mu[0] = real(0.5) * erfc(SG > 0 ? -z : z);
+  mu[1] = fmadd(U, mu[0], (real(0.5) * inv_sqrt_pi) * s2h * ex);
+  mu[2] = fmadd(U, mu[1], h * mu[0]);
+  mu[3] = fmadd(U, mu[2], real(2) * h * mu[1]);
+  mu[4] = fmadd(U, mu[3], real(3) * h * mu[2]);
+  const real G = inv_sqrt_pi * is * ex, zi = z * is;
+  const real ke = real(0.5) * (U * U + V * V), X = fmadd(V, V, K1 * h);
+  const GasSlope<real> sx = gas_slope(wn, U, V, h, ke, k), sy = gas_slope(wt, U, V, h, ke, k);
+  const real t1 = fmadd(real(0.5) * G, sy.e, slope_d1(sy, mu));
+  // ---- reverse
+  GasSlope<real> lx{0, 0, 0, 0}, ly{0, 0, 0, 0};
+  GasAdj<real> g{};
+  real ld1 = real(0), lG = real(0), lzi = real(0), lke = real(0);
+  second_moments_adj(sx, sy, mu, V, h, X, t1, k, e.lMalr, lx, ly, g, ld1);
+  first_moments_adj(sx, mu, V, X, G, zi, k, e.lWcn, real(0), lx, g, lG, lzi);
+  first_moments_adj(sy, mu, V, X, G, zi, k, e.lWct, ld1, ly, g, lG, lzi);
+  // Wc = r [mu0, mu1, V mu0, X mu0 + mu2], Flr = r [mu1, mu2, V mu1, X mu1 + mu3]
+  const real m0 = fmadd(X, e.lWc[3], fmadd(V, e.lWc[2], e.lWc[0]));
+  const real m1 = e.lWc[1] + fmadd(X, e.lFlr[3], fmadd(V, e.lFlr[2], e.lFlr[0]));
+  const real m2 = e.lWc[3] + e.lFlr[1], m3 = e.lFlr[3];
+  lq.r += m0 * mu[0] + m1 * mu[1] + m2 * mu[2] + m3 * mu[3];
+  g.mu[0] += q.r * m0;
+  g.mu[1] += q.r * m1;
+  g.mu[2] += q.r * m2;
+  g.mu[3] += q.r * m3;
+  g.V += q.r * (mu[0] * e.lWc[2] + mu[1] * e.lFlr[2]);
+  g.X += q.r * (mu[0] * e.lWc[3] + mu[1] * e.lFlr[3]);
+  gas_slope_adj(wn, U, V, h, ke, lx, k, lwn, g, lke);
+  gas_slope_adj(wt, U, V, h, ke, ly, k, lwt, g, lke);
+  moments_adj(mu, U, h, g);
+  // d mu0 = G (dU - zi dh), d mu1 = mu0 dU + G/2 dh, dG = G (-2 zi dU + (2 zi^2 - is^2) dh),
+  // dzi = is^2 (dU - 2 zi dh)
+  const real is2 = is * is, lz = lzi * is2, lg0 = g.mu[0] * G, lGG = lG * G;
+  lq.u += g.U + lg0 + g.mu[1] * mu[0] - real(2) * zi * lGG + lz + lke * U;
+  lq.v += g.V + real(2) * V * g.X + lke * V;
+  const real lh = fmadd(K1, g.X, g.h) - lg0 * zi + real(0.5) * g.mu[1] * G + lGG * (real(2) * zi * zi - is2) -
+                  real(2) * zi * lz;
+  lq.p += lh * q.ir;
+  lq.ir += lh * q.p;
 }
 
 template <class real>
@@ -927,95 +818,10 @@ DFW_HD void gks_flux_adj_sides(const real* wln, const real* wlt, const real* wrn
                                const Prim<real>& ql, const Prim<real>& qr, const Coef<real>& k,
                                const GksEqAdj<real>& e, real* lwln, real* lwlt, real* lwrn, real* lwrt,
                                PrimAdj<real>& lql, PrimAdj<real>& lqr) {
-  const real* lWc = e.lWc;
-  const real* lWcn = e.lWcn;
-  const real* lWct = e.lWct;
-  const real* lFlr = e.lFlr;
-  const real* lMalr = e.lMalr;
   lql.p += e.lpl;
   lqr.p += e.lpr;
-  // ---- reverse: the two half-space sides
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const real* wn = side == 0 ? wln : wrn;
-    const real* wt = side == 0 ? wlt : wrt;
-    real* lwn = side == 0 ? lwln : lwrn;
-    real* lwt = side == 0 ? lwlt : lwrt;
-    const Prim<real>& q = side == 0 ? ql : qr;
-    PrimAdj<real>& lq = side == 0 ? lql : lqr;
-    real lam = real(0.5) * q.r / q.p;
-    Mom<real> M;
-    maxwell_moments(q.u, q.v, lam, side == 0 ? 1 : -1, k, M);
-    real g1[4], g2[4], a[4], b[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      g1[c] = wn[c] * q.ir;
-      g2[c] = wt[c] * q.ir;
-    }
-    micro_slope(g1, q.u, q.v, lam, real(0.5) / lam, k, a);
-    micro_slope(g2, q.u, q.v, lam, real(0.5) / lam, k, b);
-    MomAdj<real> lM;
-    lM.zero();
-    real la[4] = {0, 0, 0, 0}, lb[4] = {0, 0, 0, 0};
-    real lt[4];
-    real t[4];
-    // Wc += r <psi>, Wcn += r <(a.psi) psi>, Wct += r <(b.psi) psi>
-    mom_psi(M, 0, 0, t);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lq.r += lWc[c] * t[c];
-      lt[c] = q.r * lWc[c];
-    }
-    mom_psi_adj(M, 0, 0, lt, lM);
-    mom_s_psi(M, a, 0, 0, t);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lq.r += lWcn[c] * t[c];
-      lt[c] = q.r * lWcn[c];
-    }
-    mom_s_psi_adj(M, a, 0, 0, lt, la, lM);
-    mom_s_psi(M, b, 0, 0, t);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lq.r += lWct[c] * t[c];
-      lt[c] = q.r * lWct[c];
-    }
-    mom_s_psi_adj(M, b, 0, 0, lt, lb, lM);
-    // Flr += r <u psi>, Malr += r (<(a.psi) u^2 psi> + <(b.psi) u v psi>)
-    mom_psi(M, 1, 0, t);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lq.r += lFlr[c] * t[c];
-      lt[c] = q.r * lFlr[c];
-    }
-    mom_psi_adj(M, 1, 0, lt, lM);
-    real t2[4];
-    mom_s_psi(M, a, 2, 0, t);
-    mom_s_psi(M, b, 1, 1, t2);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lq.r += lMalr[c] * (t[c] + t2[c]);
-      lt[c] = q.r * lMalr[c];
-    }
-    mom_s_psi_adj(M, a, 2, 0, lt, la, lM);
-    mom_s_psi_adj(M, b, 1, 1, lt, lb, lM);
-    real lU = real(0), lV = real(0), llam = real(0);
-    real lg1[4] = {0, 0, 0, 0}, lg2[4] = {0, 0, 0, 0};
-    micro_slope_adj(g1, q.u, q.v, lam, k, la, lg1, lU, lV, llam);
-    micro_slope_adj(g2, q.u, q.v, lam, k, lb, lg2, lU, lV, llam);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      lwn[c] += lg1[c] * q.ir;
-      lwt[c] += lg2[c] * q.ir;
-      lq.ir += lg1[c] * wn[c] + lg2[c] * wt[c];
-    }
-    maxwell_moments_adj(M, side == 0 ? 1 : -1, k, lM, lU, lV, llam);
-    lq.u += lU;
-    lq.v += lV;
-    // lam = r / (2 p)
-    lq.r += llam * real(0.5) / q.p;
-    lq.p += -llam * lam / q.p;
-  }
+  gks_side_adj<1>(ql, wln, wlt, k, e, lwln, lwlt, lql);
+  gks_side_adj<-1>(qr, wrn, wrt, k, e, lwrn, lwrt, lqr);
 }
 
 template <class real>

@@ -217,53 +217,6 @@ DFW_HD Basis<real> recon_basis(const real* wa, const real* wb, const Coef<real>&
 //   paper's zero-mean quadratic with x0 = -dx/2, x1 = dx^2/3 written through p_1.
 // NDEG limits the coefficients produced (2 = value and slope at the edge only).
 // ------------------------------------------------------------------------------------------------
-// Smoothness indicators beta_0..beta_3 of eq. (38) of the four WENO-AO stencils of a cell (five
-// averages Q[0..4] = Q_{i-2..i+2}): Jiang-Shu forms for the three quadratics, closed form for the
-// quartic.  The differences they are built from are kept, since they also determine the candidate
-// polynomials: t_k is the second difference of stencil k (twice the xi^2 coefficient of p_k), s_k
-// twice the slope of p_k at the cell centre (with the sign of its Jiang-Shu form: +p_0', -p_1',
-// -p_2'), and u_1..u_4 the coefficients of the quartic in its Legendre-type basis on the cell: in
-// zeta = xi + 1/2 its zeta^1..zeta^4 coefficients are u_1 - 3/20 u_3, u_2 - 3/14 u_4, u_3 and u_4.
-// ------------------------------------------------------------------------------------------------
-template <class real>
-struct WenoTerms {
-  real b[4];
-  real t0, t1, t2, s0, s1, s2, u1, u2, u3, u4;
-};
-
-template <class real>
-DFW_HD WenoTerms<real> weno_terms(const real* Q) {
-  const real Q0 = Q[0], Q1 = Q[1], Q2 = Q[2], Q3 = Q[3], Q4 = Q[4];
-  const real k1312 = real(13.0 / 12.0), k14 = real(0.25);
-  WenoTerms<real> T;
-  T.t0 = Q0 - real(2) * Q1 + Q2;
-  T.t1 = Q1 - real(2) * Q2 + Q3;
-  T.t2 = Q2 - real(2) * Q3 + Q4;
-  T.s0 = Q0 - real(4) * Q1 + real(3) * Q2;
-  T.s1 = Q1 - Q3;
-  T.s2 = T.t2 - real(2) * (Q3 - Q2);  // 3 Q2 - 4 Q3 + Q4
-  T.b[0] = k1312 * T.t0 * T.t0 + k14 * T.s0 * T.s0;
-  T.b[1] = k1312 * T.t1 * T.t1 + k14 * T.s1 * T.s1;
-  T.b[2] = k1312 * T.t2 * T.t2 + k14 * T.s2 * T.s2;
-  // the quartic's coefficients from the same differences (exact identities of its cell-average fit)
-  const real d40 = Q4 - Q0;
-  T.u1 = (real(-11) * d40 - real(82) * T.s1) * real(1.0 / 120.0);
-  T.u2 = (real(34) * T.t1 - real(3) * (T.t0 + T.t2)) * real(1.0 / 56.0);
-  T.u3 = (real(2) * T.s1 + d40) * real(1.0 / 12.0);
-  T.u4 = (T.t0 - real(2) * T.t1 + T.t2) * real(1.0 / 24.0);
-  const real e1 = T.u1 + real(0.1) * T.u3;
-  const real e2 = T.u2 + real(123.0 / 455.0) * T.u4;
-  T.b[3] = e1 * e1 + real(13.0 / 3.0) * e2 * e2 + real(781.0 / 20.0) * T.u3 * T.u3 +
-           real(1421461.0 / 2275.0) * T.u4 * T.u4;
-  return T;
-}
-
-template <class real>
-DFW_HD void weno_indicators(const real* Q, real* b) {
-  const WenoTerms<real> T = weno_terms(Q);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) b[q] = T.b[q];
-}
 
 // ------------------------------------------------------------------------------------------------
 // Non-linear time limiter (Section 2.2, eqs. (27)-(29)).  Weight of one reconstruction:
@@ -271,23 +224,8 @@ DFW_HD void weno_indicators(const real* Q, real* b) {
 //   alpha = 2 a2 / (a1 + a2)  (in (0, 1]: 1 on smooth data, -> 0 across a jump),
 // beta_min, beta_max over the four indicators of eq. (38), tau_Z of eq. (37).  The weight of an
 // interface is the smallest over the characteristic components of the two normal reconstructions
-// beside it; recon_poly hands it out of the normal sweep (from the ratios tau/(beta_k + eps) that
-// its WENO-Z weights already hold, or from this function where the DF branch skips them).
+// beside it; ao_weights forms it from the ratios tau/(beta_k + eps) that its weights hold.
 // ------------------------------------------------------------------------------------------------
-template <class real>
-DFW_HD real time_limiter_weight(const real* Q, const Coef<real>& k) {
-  real b[4];
-  weno_indicators(Q, b);
-  const real tau = (fabs(b[3] - b[0]) + fabs(b[3] - b[1]) + fabs(b[3] - b[2])) * real(1.0 / 3.0);
-  real bmin = b[0] < b[1] ? b[0] : b[1], bmax = b[0] > b[1] ? b[0] : b[1];
-  bmin = bmin < b[2] ? bmin : b[2];
-  bmin = bmin < b[3] ? bmin : b[3];
-  bmax = bmax > b[2] ? bmax : b[2];
-  bmax = bmax > b[3] ? bmax : b[3];
-  const real x1 = tau / (bmin + k.eps), x2 = tau / (bmax + k.eps);
-  const real a1 = real(1) + x1 * x1, a2 = real(1) + x2 * x2;
-  return real(2) * a2 / (a1 + a2);
-}
 
 // ------------------------------------------------------------------------------------------------
 // Difference form of the reconstruction.  With d_m = Q_{m+1} - Q_m (four differences of the five
@@ -300,6 +238,8 @@ DFW_HD real time_limiter_weight(const real* Q, const Coef<real>& k) {
 // Since wb_k - wb_3 d_k/d_3 = d_k (r_k^2 - r_3^2) / sum w and the d_k sum to one, the weights of the
 // combination are a_k = d_k (r_k^2 - r_3^2) and H = 1 + r_3^2 over sum w = H + a_0 + a_1 + a_2, and the
 // combination is the centred quadratic p_1 corrected by x01 and x12.  a_1 only enters the sum.
+// (The beta_k: Jiang-Shu forms for the quadratics, closed form for the quartic, with u_1..u_4 its
+// coefficients in its Legendre-type basis on the cell.)
 // The 16 reconstructions of an interface are most of the interface kernel's arithmetic, and the kernel
 // is bound by instruction issue: this form takes about 76 (edge, two sides sharing t_k and
 // 13/12 t_k^2 + eps) and 88 (Gauss points) instructions against 137 and 147 for the evaluation
@@ -380,6 +320,24 @@ DFW_HD AoWeights<real> ao_weights(real d1, real d2, real t0, real t1, real t2, r
   A.H = real(1) + s3;
   A.is = rcp_pos((A.H + A.a0) + (A.a1 + A.a2));
   return A;
+}
+
+// The smoothness indicators beta_0..beta_3 of five averages.
+template <class real>
+struct WenoTerms {
+  real b[4];
+};
+
+template <class real>
+DFW_HD WenoTerms<real> weno_terms(const real* Q) {
+  const real d1 = Q[2] - Q[1], d2 = Q[3] - Q[2];
+  const real t0 = d1 - (Q[1] - Q[0]), t1 = d2 - d1, t2 = (Q[4] - Q[3]) - d2;
+  Coef<real> k{};
+  k.eps = real(1);
+  const AoWeights<real> A = ao_weights(d1, d2, t0, t1, t2, beta_curv(t0, k), beta_curv(t1, k), beta_curv(t2, k), k);
+  const real c = real(13.0 / 12.0);
+  return {{A.h0 * A.h0 + c * t0 * t0, A.h1 * A.h1 + c * t1 * t1, A.h2 * A.h2 + c * t2 * t2,
+           A.e1 * A.e1 + c * A.e2 * A.e2 + real(kBetaU) * A.u * A.u + real(kBetaV) * A.v * A.v}};
 }
 
 // The hybrid reconstruction of one cell at its edge xi = 0: value minus cell average (dv) and slope
@@ -569,126 +527,8 @@ DFW_HD void lf_flux(const real* wl, const real* wlx, const real* wly, const real
 // ------------------------------------------------------------------------------------------------
 // Gas-kinetic flux (Sections 2.2 and 3.4), Euler case: physical tau = 0 outside the exponential,
 // numerical tau_n = c1 dt + c2 |(pl-pr)/(pl+pr)| dt inside it.
-// Moments <u^a v^b xi^2c> of a Maxwellian (normalised by rho) factorise as mu[a] mv[b] mx[c].
+// Moments <u^a v^b xi^2c> of a Maxwellian (normalised by rho) factorise; mu_n are those of u.
 // ------------------------------------------------------------------------------------------------
-template <class real>
-struct Mom {
-  real mu[7];  // u-moments 0..6 (full space, or one half space)
-  real mv[6];  // v-moments 0..5 (full space)
-  real mx[3];  // <xi^0>, <xi^2>, <xi^4>
-  real U, V, lam, h;  // h = 1 / (2 lam)
-};
-
-template <class real>
-DFW_HD void full_recursion(real* m, int from, int to, real U, real h) {
-  // m[n+2] = U m[n+1] + (n+1) h m[n], h = 1/(2 lambda)
-  for (int n = from; n + 2 <= to; ++n) m[n + 2] = U * m[n + 1] + real(n + 1) * h * m[n];
-}
-
-// side: 0 full space, +1 u > 0, -1 u < 0.  h = 1/(2 lam), which the callers form as p/rho from the
-// reciprocal of the density they already hold (the same value as 0.5/lam, also for p = 0 and on
-// failing states, without a division).
-template <class real>
-DFW_HD void maxwell_moments(real U, real V, real lam, real h, int side, const Coef<real>& k, Mom<real>& M) {
-  M.U = U;
-  M.V = V;
-  M.lam = lam;
-  M.h = h;
-  if (side == 0) {
-    M.mu[0] = real(1);
-    M.mu[1] = U;
-  } else {
-    const real inv_sqrt_pi = real(0.56418958354775628695);
-    real sl = sqrt(lam);
-    real g = real(0.5) * exp(-lam * U * U) * inv_sqrt_pi / sl;
-    if (side > 0) {
-      M.mu[0] = real(0.5) * erfc(-sl * U);
-      M.mu[1] = U * M.mu[0] + g;
-    } else {
-      M.mu[0] = real(0.5) * erfc(sl * U);
-      M.mu[1] = U * M.mu[0] - g;
-    }
-  }
-  full_recursion(M.mu, 0, 6, U, h);
-  M.mv[0] = real(1);
-  M.mv[1] = V;
-  full_recursion(M.mv, 0, 5, V, h);
-  M.mx[0] = real(1);
-  M.mx[1] = k.K * h;
-  M.mx[2] = k.K * (k.K + real(2)) * h * h;
-}
-
-template <class real>
-DFW_HD void maxwell_moments(real U, real V, real lam, int side, const Coef<real>& k, Mom<real>& M) {
-  maxwell_moments(U, V, lam, real(0.5) / lam, side, k, M);
-}
-
-template <class real>
-DFW_HD real mom(const Mom<real>& M, int a, int b, int c) {
-  return M.mu[a] * M.mv[b] * M.mx[c];
-}
-
-// <(s . psi) u^a v^b xi^2c>, s . psi = s0 + s1 u + s2 v + s3 (u^2 + v^2 + xi^2)/2.  With the v- and
-// xi-moments folded first it is a three-term form in the u-moments,
-//   <(s . psi) u^a v^b xi^2c> = A mu[a] + B mu[a+1] + C mu[a+2],
-//   A = s0 mv[b] mx[c] + s2 mv[b+1] mx[c] + s3/2 (mv[b+2] mx[c] + mv[b] mx[c+1]),
-//   B = s1 mv[b] mx[c],  C = s3/2 mv[b] mx[c],
-// whose coefficients depend on (s, b, c) only: calls with the same slope and v-power share them.
-template <class real>
-struct SForm {
-  real A, B, C;
-};
-
-template <class real>
-DFW_HD SForm<real> s_form(const Mom<real>& M, const real* s, int b, int c) {
-  const real vx = M.mv[b] * M.mx[c];
-  const real hs3 = real(0.5) * s[3];
-  SForm<real> f;
-  f.A = s[0] * vx + s[2] * (M.mv[b + 1] * M.mx[c]) + hs3 * (M.mv[b + 2] * M.mx[c] + M.mv[b] * M.mx[c + 1]);
-  f.B = s[1] * vx;
-  f.C = hs3 * vx;
-  return f;
-}
-
-template <class real>
-DFW_HD real s_apply(const SForm<real>& f, const real* mu, int a) {
-  return f.A * mu[a] + f.B * mu[a + 1] + f.C * mu[a + 2];
-}
-
-// <(s . psi) u^a v^b psi>  (4 components)
-template <class real>
-DFW_HD void mom_s_psi(const Mom<real>& M, const real* s, int a, int b, real* out) {
-  const SForm<real> f0 = s_form(M, s, b, 0), f1 = s_form(M, s, b + 1, 0), f2 = s_form(M, s, b + 2, 0);
-  const SForm<real> fx = s_form(M, s, b, 1);
-  out[0] = s_apply(f0, M.mu, a);
-  out[1] = s_apply(f0, M.mu, a + 1);
-  out[2] = s_apply(f1, M.mu, a);
-  out[3] = real(0.5) * (s_apply(f0, M.mu, a + 2) + s_apply(f2, M.mu, a) + s_apply(fx, M.mu, a));
-}
-
-// <u^a v^b psi>
-template <class real>
-DFW_HD void mom_psi(const Mom<real>& M, int a, int b, real* out) {
-  out[0] = mom(M, a, b, 0);
-  out[1] = mom(M, a + 1, b, 0);
-  out[2] = mom(M, a, b + 1, 0);
-  out[3] = real(0.5) * (mom(M, a + 2, b, 0) + mom(M, a, b + 2, 0) + mom(M, a, b, 1));
-}
-
-// Micro-slope s with <(s . psi) psi> = g (g = dW / rho), closed-form inverse of the moment matrix;
-// h = 1 / (2 lam).
-template <class real>
-DFW_HD void micro_slope(const real* g, real U, real V, real lam, real h, const Coef<real>& k, real* s) {
-  real B = U * U + V * V + k.K2 * h;
-  real R4 = real(2) * g[3] - B * g[0];
-  real R3 = g[2] - V * g[0];
-  real R2 = g[1] - U * g[0];
-  s[3] = k.k4K2 * (lam * lam) * (R4 - real(2) * U * R2 - real(2) * V * R3);
-  s[2] = real(2) * lam * R3 - V * s[3];
-  s[1] = real(2) * lam * R2 - U * s[3];
-  s[0] = g[0] - U * s[1] - V * s[2] - real(0.5) * s[3] * B;
-}
-
 // The slopes of a Maxwellian enter the flux only through moments <(s . psi) u^a v^b psi>, and since
 // rho (s . psi) g is the derivative of rho g in that direction, such a moment is the derivative of
 // rho <u^a v^b psi>, a product of u-moments mu_n(U, h) with polynomials in V and h = p/rho.  So no slope s is formed: with the derivative's density r = rho_x, a = rho U_x,

@@ -87,7 +87,10 @@ DFW_HD Basis<real> recon_basis(const real* wa, const real* wb, const Coef<real>&
 }
 
 // Smoothness indicators beta_0..beta_3 of eq. (38) and the differences that determine the candidate
-// polynomials (see WenoTerms of dfw_math.hpp for the terms).
+// polynomials: t_k is the second difference of stencil k (twice the xi^2 coefficient of p_k), s_k
+// twice the slope of p_k at the cell centre (with the sign of its Jiang-Shu form: +p_0', -p_1',
+// -p_2'), and u_1..u_4 the coefficients of the quartic in its Legendre-type basis on the cell: in
+// zeta = xi + 1/2 its zeta^1..zeta^4 coefficients are u_1 - 3/20 u_3, u_2 - 3/14 u_4, u_3 and u_4.
 template <class real>
 struct WenoTerms {
   real b[4];

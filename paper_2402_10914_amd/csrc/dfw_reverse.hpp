@@ -338,14 +338,14 @@ __global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) 
   real lwr[4] = {0, 0, 0, 0}, lwrn[4] = {0, 0, 0, 0}, lwrt[4] = {0, 0, 0, 0};
   const real ldf = STAGE == 2 ? ldfp * df_other : real(0);
   if constexpr (FLUX == 0) {
-    if (seg) gp_flux_adj<real, FLUX>(wl, wln, wlt, wr, wrn, wrt, dt, k, lFs, lFts, ldf, lwl, lwln, lwlt, lwr, lwrn, lwrt);
+    if (seg) gp_flux_adj<real, FLUX>(wl, wln, wlt, wr, wrn, wrt, dt, k, STAGE == 1 ? lFs : nullptr, lFts, ldf, lwl, lwln, lwlt, lwr, lwrn, lwrt);
   } else {
     // The gas-kinetic reverse in two halves around a barrier: the Gauss point's 24 states and the 22
     // values handed from the equilibrium-state reverse to the side reverse wait in the lane's own
     // LDS slots (the exchange buffers hold nothing else between the seeds and the segment reverse),
     // so that neither half holds the other's live values; the barrier makes the compiler reload them.
     GksEqAdj<real> e{};
-    if (seg) gks_flux_adj_eq(wln, wlt, wrn, wrt, prim(wl, k), prim(wr, k), dt, k, lFs, lFts, e);
+    if (seg) gks_flux_adj_eq(wln, wlt, wrn, wrt, prim(wl, k), prim(wr, k), dt, k, STAGE == 1 ? lFs : nullptr, lFts, e);
     __syncthreads();  // every lane has read its staged seeds from the exchange buffer
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
