@@ -68,9 +68,9 @@ __device__ __forceinline__ real pair_swap(real x) {
 // Thread 2p + s works on side s of interface segment p (s = 0: the cell before the interface).
 // RULE >= 0 fixes the hybrid switch rule at compile time (its selects fold away: this kernel is at
 // the register limit and pays for every live value); RULE < 0 reads the rule of S at run time.
-// The LF 2-interface tile asks for two waves per SIMD (see kAdjShapes).
+// The 2-interface tile asks for two waves per SIMD (see kAdjShapes).
 template <class real, int FLUX, int STAGE, int TF, int TR, int RULE>
-__global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) void k_adj_faces(
+__global__ __launch_bounds__(2 * TF * (TR + 4), TF == 2 ? 2 : 1) void k_adj_faces(
     const real* __restrict__ W, const real* __restrict__ alpha, const real* __restrict__ P,
     const real* __restrict__ Q, const real* __restrict__ LA, const real* __restrict__ DX,
     const real* __restrict__ DY, real* __restrict__ BX, real* __restrict__ BY, GridDesc G, Scheme S,
@@ -81,7 +81,6 @@ __global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) 
   __shared__ real sL[4][2 * TF * T::NQ];  // line values, the two sides of a segment side by side
   __shared__ real sX[5][4][T::NT];         // exchange of line adjoints between rows (m = 0..4)
   __shared__ real sN[4][T::NT];            // each lane's normal-derivative adjoints, parked
-  __shared__ real sE[FLUX == 1 ? 22 : 1][T::NT];  // the gas-kinetic reverse's hand-over, parked
 
   int b = xcd_tile(blockIdx.x, gridDim.x);  // neighbouring tiles share an XCD (and its L2)
   const int nbx = tiles_x<TF, TR>(G.nx, G.ny);
@@ -338,14 +337,14 @@ __global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) 
   real lwr[4] = {0, 0, 0, 0}, lwrn[4] = {0, 0, 0, 0}, lwrt[4] = {0, 0, 0, 0};
   const real ldf = STAGE == 2 ? ldfp * df_other : real(0);
   if constexpr (FLUX == 0) {
-    if (seg) gp_flux_adj<real, FLUX>(wl, wln, wlt, wr, wrn, wrt, dt, k, STAGE == 1 ? lFs : nullptr, lFts, ldf, lwl, lwln, lwlt, lwr, lwrn, lwrt);
+    if (seg)
+      gp_flux_adj<real, FLUX>(wl, wln, wlt, wr, wrn, wrt, dt, k, STAGE == 1 ? lFs : nullptr, lFts, ldf, lwl, lwln, lwlt,
+                              lwr, lwrn, lwrt);
   } else {
-    // The gas-kinetic reverse in two halves around a barrier: the Gauss point's 24 states and the 22
-    // values handed from the equilibrium-state reverse to the side reverse wait in the lane's own
-    // LDS slots (the exchange buffers hold nothing else between the seeds and the segment reverse),
-    // so that neither half holds the other's live values; the barrier makes the compiler reload them.
-    GksEqAdj<real> e{};
-    if (seg) gks_flux_adj_eq(wln, wlt, wrn, wrt, prim(wl, k), prim(wr, k), dt, k, STAGE == 1 ? lFs : nullptr, lFts, e);
+    // The gas-kinetic reverse in two halves around a barrier: the Gauss point's 24 states wait in the
+    // lane's own slots of the exchange buffers (which hold nothing else between the seeds and the
+    // segment reverse) for the second half; the barrier makes the compiler reload them there instead
+    // of holding them through the first.
     __syncthreads();  // every lane has read its staged seeds from the exchange buffer
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -355,14 +354,9 @@ __global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) 
       sX[3][c][tid] = wrn[c];
       sX[4][c][tid] = wlt[c];
       sN[c][tid] = wrt[c];
-      sE[c][tid] = e.lWc[c];
-      sE[4 + c][tid] = e.lWcn[c];
-      sE[8 + c][tid] = e.lWct[c];
-      sE[12 + c][tid] = e.lFlr[c];
-      sE[16 + c][tid] = e.lMalr[c];
     }
-    sE[20][tid] = e.lpl;
-    sE[21][tid] = e.lpr;
+    GksEqAdj<real> e{};
+    if (seg) gks_flux_adj_eq(wln, wlt, wrn, wrt, prim(wl, k), prim(wr, k), dt, k, STAGE == 1 ? lFs : nullptr, lFts, e);
     __syncthreads();
     if (seg) {
       real vl[4], vr[4], vln[4], vrn[4], vlt[4], vrt[4];
@@ -374,14 +368,7 @@ __global__ __launch_bounds__(2 * TF * (TR + 4), (FLUX == 0 && TF == 2) ? 2 : 1) 
         vrn[c] = sX[3][c][tid];
         vlt[c] = sX[4][c][tid];
         vrt[c] = sN[c][tid];
-        e.lWc[c] = sE[c][tid];
-        e.lWcn[c] = sE[4 + c][tid];
-        e.lWct[c] = sE[8 + c][tid];
-        e.lFlr[c] = sE[12 + c][tid];
-        e.lMalr[c] = sE[16 + c][tid];
       }
-      e.lpl = sE[20][tid];
-      e.lpr = sE[21][tid];
       const Prim<real> ql = prim(vl, k), qr = prim(vr, k);
       PrimAdj<real> lql, lqr;
       lql.zero();
@@ -659,9 +646,9 @@ struct AdjShape {
 };
 // Interface tiles of the adjoint kernel, per flux (LF, GKS): 2 interfaces x 60 rows, 256 threads.
 // The 60-row tile recomputes the segment adjoint (the costly part, above all with the GKS flux) for
-// 64 segment rows per 60 owned.  The LF kernel is held to two waves per SIMD (launch bounds), so that
-// two workgroups share a compute unit and one's barriers and staging overlap the other's arithmetic;
-// the GKS kernel needs one wave per SIMD with its accumulation registers as well, and 121 KB of LDS.
+// 64 segment rows per 60 owned.  Both kernels are held to two waves per SIMD (launch bounds; 248 to
+// 251 registers, no spills) and take 76 KB of LDS, so that two workgroups share a compute unit and
+// one's barriers and staging overlap the other's arithmetic.
 static constexpr AdjShape kAdjShapes[2] = {{2, 60}, {2, 60}};
 
 static int adj_tiles(int flux, int nx, int ny) {
