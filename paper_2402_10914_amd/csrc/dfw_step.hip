@@ -61,6 +61,23 @@ __device__ __forceinline__ double bank_max(const Ctrl* ctrl, int bank) {
   return v;
 }
 
+// Reads one word of every 64-byte line of a kernel's first BYTES of arguments, all at once.  The
+// arguments are otherwise loaded where they are first used, one round trip after another in a kernel
+// whose blocks follow each other; after this they come from the scalar cache.  Launches of few
+// workgroups are bound by such chains: 20 steps of a 64 x 64 LF grid in FP64 870 -> 848 us, 512^2
+// GKS 0.8 % faster, 4096^2 GKS the same.  The FP32 interface kernel goes without: its five waves per
+// SIMD hide the chain, and 4096^2 LF ran 1.5 % slower with it.
+template <int BYTES>
+__device__ __forceinline__ void touch_arguments() {
+  const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int kLines = (BYTES + 63) / 64;
+  static_assert(kLines >= 1 && kLines <= 8, "more lines than read here");
+  int w[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) w[i] = p[16 * (i < kLines ? i : 0)];
+  asm volatile("" ::"s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]), "s"(w[6]), "s"(w[7]));
+}
+
 // One grid: sizes, spacing, boundaries and element offsets of its arrays inside the (packed) state,
 // alpha, stage and interface buffers.
 struct GridDesc {
@@ -165,6 +182,8 @@ struct Tile {
 template <int TF, int TR>
 __host__ __device__ inline int tiles_x(int nx, int ny) { return ((nx + 1 + TF - 1) / TF) * ((ny + TR - 1) / TR); }
 
+constexpr int kFaceArgs = 6 * 8 + (int)sizeof(GridDesc) + 2 * 8 + (int)sizeof(Scheme);  // through S
+
 template <class real, int FLUX, int OUT, int TF, int TR>
 __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict__ Wall, const real* __restrict__ Aall,
                                                          real* __restrict__ FXall, real* __restrict__ FYall,
@@ -173,6 +192,7 @@ __global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict_
                                                          const int4* __restrict__ tiles, Scheme S, double dt_host,
                                                          int lead, int step, int nsteps, double* __restrict__ dt_hist) {
   using T = Tile<TF, TR>;
+  if constexpr (sizeof(real) == 8) touch_arguments<kFaceArgs>();
   __shared__ real sW[4][T::NR][T::WN];
   __shared__ real sA[T::NR][T::AN];
   __shared__ real sLine[8][T::NT];
@@ -472,6 +492,7 @@ __global__ __launch_bounds__(kCellBlock) void k_update1(const real* __restrict__
                                                         real* __restrict__ Rall, Ctrl* __restrict__ ctrls, GridDesc G0,
                                                         const GridDesc* __restrict__ grids,
                                                         const int2* __restrict__ cblocks, int step, int tl) {
+  touch_arguments<6 * 8 + (int)sizeof(GridDesc) + 2 * 8>();
   const CellCtx C = cell_ctx(G0, grids, cblocks);
   Ctrl* ctrl = ctrls + C.gi;
   if (ctrl->fail_at <= step || !(ctrl->dt > 0.0) || !C.live) return;
@@ -578,6 +599,7 @@ __global__ __launch_bounds__(kCellBlock) void k_update2(real* __restrict__ Wall,
                                                         const real* __restrict__ FYall, Ctrl* __restrict__ ctrls,
                                                         GridDesc G0, const GridDesc* __restrict__ grids,
                                                         const int2* __restrict__ cblocks, Scheme S, int step) {
+  touch_arguments<6 * 8 + (int)sizeof(GridDesc) + 2 * 8>();
   const CellCtx C = cell_ctx(G0, grids, cblocks);
   Ctrl* ctrl = ctrls + C.gi;
   const double dtd = ctrl->dt;
@@ -611,6 +633,7 @@ __global__ __launch_bounds__(kCellBlock) void k_rk_stage(const real* __restrict_
                                                          real* __restrict__ Uall, Ctrl* __restrict__ ctrls, GridDesc G0,
                                                          const GridDesc* __restrict__ grids,
                                                          const int2* __restrict__ cblocks, int step) {
+  touch_arguments<6 * 8 + (int)sizeof(GridDesc) + 2 * 8>();
   const CellCtx C = cell_ctx(G0, grids, cblocks);
   Ctrl* ctrl = ctrls + C.gi;
   if (ctrl->fail_at <= step || !(ctrl->dt > 0.0) || !C.live) return;
@@ -641,6 +664,7 @@ __global__ __launch_bounds__(kCellBlock) void k_rk_final(real* __restrict__ Wall
                                                          const real* __restrict__ FYall, Ctrl* __restrict__ ctrls,
                                                          GridDesc G0, const GridDesc* __restrict__ grids,
                                                          const int2* __restrict__ cblocks, Scheme S, int step) {
+  touch_arguments<6 * 8 + (int)sizeof(GridDesc) + 2 * 8>();
   const CellCtx C = cell_ctx(G0, grids, cblocks);
   Ctrl* ctrl = ctrls + C.gi;
   const double dtd = ctrl->dt;
