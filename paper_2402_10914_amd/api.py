@@ -35,7 +35,7 @@ class Params:
     eps_weno: float = 1e-6
     c1: float = 0.01
     c2: float = 5.0
-    tile: int = 0  # interface tile shape (performance only; see tile_shapes())
+    tile: int = 0  # interface tile shape (performance only; see tile_shapes()); 0: the library chooses by size
     time_limiter: int = 0  # 1: non-linear time limiter of Section 2.2, eqs. (27)-(29)
     time_scheme: int = TIME_S2O4  # TIME_SSPRK3: eq. (32) of Section 2.3 (LF flux only)
     t_end: float = 0.0  # > 0: stop at this time (the last step is shortened; nsteps is an upper bound)

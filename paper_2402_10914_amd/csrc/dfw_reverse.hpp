@@ -743,9 +743,10 @@ static AdjLayout adj_layout(const dfw_grid* g, size_t es, int every) {
 // before every step n that starts a segment; with ckpt_every = 1 also the W* and the stage-2 DF
 // products of step n (still in the workspace until step n + 1 starts) into slot n.
 template <class real>
-static dfw_status run_ckpt_impl(real* W, real* A, const dfw_grid* g, const dfw_params* p, int nsteps, int every,
+static dfw_status run_ckpt_impl(real* W, real* A, const dfw_grid* g, const dfw_params* params, int nsteps, int every,
                                 char* ckpt, char* ws, double* dt_hist, double* t_out, int32_t* fail_step,
                                 hipStream_t st) {
+  const dfw_params q = with_shape(params, g, 1), *p = &q;
   const size_t es = sizeof(real);
   const size_t N = (size_t)g->nx * g->ny;
   WsLayout L = layout(g, es);
@@ -793,9 +794,10 @@ static dfw_status run_ckpt_impl(real* W, real* A, const dfw_grid* g, const dfw_p
 }
 
 template <class real, int FLUX>
-static dfw_status adjoint_impl(const dfw_grid* g, const dfw_params* p, int nsteps, int every, const char* ckpt,
+static dfw_status adjoint_impl(const dfw_grid* g, const dfw_params* params, int nsteps, int every, const char* ckpt,
                                const double* dt_hist, const real* gW_final, const real* gA_final, real* gW0,
                                real* gA0, char* ws, hipStream_t st) {
+  const dfw_params q = with_shape(params, g, 1), *p = &q;
   const size_t es = sizeof(real);
   const size_t N = (size_t)g->nx * g->ny;
   const AdjLayout L = adj_layout(g, es, every);

@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -752,6 +753,8 @@ static dfw_status fail(dfw_status s, const std::string& msg) {
   return s;
 }
 
+constexpr int kMaxDevices = 64;
+
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Event-based per-kernel timing for benchmarks (see dfw_profile).
@@ -788,16 +791,64 @@ static void timed(int kind, hipStream_t st, Launch launch) {
   if (ok_a && ok_b) g_prof.recs.push_back({kind, a, b});  // a launch without both events is not timed
 }
 
-// Interface tile shapes (TF interfaces x TR segments); index 0 is the library default.
+// Interface tile shapes (TF interfaces x TR segments); index 0 leaves the choice to the library
+// (default_shape: this shape, or another that suits the launch's size).
 struct TileShape {
   int tf, tr;
 };
 static const TileShape kShapes[] = {{8, 28}, {16, 28}, {8, 60}, {16, 12}, {4, 60}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
+static int compute_units() {
+  static std::atomic<int> cached[kMaxDevices];
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+  n = cached[dev].load(std::memory_order_relaxed);
+  if (!n) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) return 256;
+    cached[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
+// The shape behind tile index 0, from the number of tiles n0, n3, n4 that the 8x28, 16x12 and 4x60 shapes
+// (256 threads each) need for the whole launch.  Results do not depend on it.  Measured, us per LF step in
+// FP64 unless noted, 8x28 / 16x12 / 4x60:
+//   a tile per compute unit or less (n3 <= units): the short 16x12 tile has the shortest way from its
+//     loads to its stores: 64^2 47 / 35 / 55, 100^2 34 / 33 / 34 (160^2, just above: 34 / 40 / 34);
+//   up to four 8x28 tiles per unit (all resident, or one round and a tail): the shape with fewer
+//     tiles: 200x150 57 / 44 / 45, 256^2 65 / 56 / 55, 300^2 72 / 70 / 62 (a batch of eight grids of 32 to
+//     128 cells, which needs more of the tall tiles: 357 / 349 / 411);
+//   from 24 per unit on the 4x60 tile, whose lanes idle less in the tangential phase, if it saves
+//     4 % of the tiles: 2048^2 1734 / 1897 / 1670, 4096^2 in FP32 5509 / 6143 / 5226, 1001x750 GKS in
+//     FP32 447 / 495 / 428 (1024^2, where it saves 3 %: 452 / 494 / 465);
+//   in between 8x28, which stages less: 512^2 133 / 153 / 135, GKS 174 / 205 / 178.
+static int default_shape(long long n0, long long n3, long long n4) {
+  const long long units = compute_units();
+  if (n3 <= units) return 3;
+  if (n0 <= 4 * units) return n4 <= n0 ? 4 : 0;
+  if (n0 >= 24 * units) return 25 * n4 <= 24 * n0 ? 4 : 0;
+  return 0;
+}
+
 static int shape_tiles(int shape, int nx, int ny) {
   const TileShape s = kShapes[shape];
   return ((nx + 1 + s.tf - 1) / s.tf) * ((ny + s.tr - 1) / s.tr) + ((ny + 1 + s.tf - 1) / s.tf) * ((nx + s.tr - 1) / s.tr);
+}
+
+// The params of a call on the grids [grids, grids + n) with tile index 0 replaced by the shape chosen.
+static dfw_params with_shape(const dfw_params* p, const dfw_grid* grids, int n) {
+  dfw_params q = *p;
+  if (q.tile == 0) {
+    long long n0 = 0, n3 = 0, n4 = 0;
+    for (int g = 0; g < n; ++g) {
+      n0 += shape_tiles(0, grids[g].nx, grids[g].ny);
+      n3 += shape_tiles(3, grids[g].nx, grids[g].ny);
+      n4 += shape_tiles(4, grids[g].nx, grids[g].ny);
+    }
+    q.tile = default_shape(n0, n3, n4);
+  }
+  return q;
 }
 
 struct FaceLaunch {
@@ -1065,9 +1116,10 @@ static void enqueue_steps(real* W, real* A, real* Ws, real* R, real* FX, real* F
 }
 
 template <class real>
-static dfw_status run_impl(real* W, real* A, const dfw_grid* g, const dfw_params* p, int nsteps, char* ws,
+static dfw_status run_impl(real* W, real* A, const dfw_grid* g, const dfw_params* params, int nsteps, char* ws,
                            double* dt_hist, double* t_out, int32_t* fail_step, hipStream_t st) {
   WsLayout L = layout(g, sizeof(real));
+  const dfw_params q = with_shape(params, g, 1), *p = &q;
   Ctrl* ctrl = (Ctrl*)(ws + L.ctrl_off);
   const GridDesc G = make_desc(g);
   enqueue_steps<real>(W, A, (real*)(ws + L.ws_off), (real*)(ws + L.r_off), (real*)(ws + L.fx_off),
@@ -1219,7 +1271,6 @@ dfw_status dfw_run(void* W, void* alpha, const dfw_grid* grid, const dfw_params*
 static __device__ __align__(256) unsigned char scratch[DFW_NOALLOC_SCRATCH_BYTES];
 
 namespace dfw {
-constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1302,10 +1353,10 @@ dfw_status dfw_rhs(const void* W, const void* alpha, const dfw_grid* grid, const
   Ctrl* ctrl = (Ctrl*)((char*)ws + Lw.ctrl_off);
   const GridDesc G = make_desc(grid);
   FaceLaunch FL;
-  FL.shape = params->tile;
+  FL.shape = with_shape(params, grid, 1).tile;
   FL.flux = params->flux;
   FL.out = OUT_F | OUT_FT | OUT_DF;
-  FL.nblocks = shape_tiles(params->tile, grid->nx, grid->ny);
+  FL.nblocks = shape_tiles(FL.shape, grid->nx, grid->ny);
   FL.tiles = nullptr;
   FL.grids = nullptr;
   FL.G0 = G;
@@ -1373,6 +1424,7 @@ dfw_status dfw_batch_plan(const dfw_grid* grids, int32_t ngrids, const dfw_param
     delete b;
     return fail(DFW_EINVAL, "batch too large (more than 2^38 cells)");
   }
+  b->params = with_shape(params, grids, ngrids);
   build_tiles(b, order);
   // one launch covers every tile (cell block) of the batch: the work items of a launch must stay below
   // 2^32, and the block counts are passed to the launch as int
