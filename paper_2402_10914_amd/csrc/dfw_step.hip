@@ -185,8 +185,11 @@ __host__ __device__ inline int tiles_x(int nx, int ny) { return ((nx + 1 + TF - 
 
 constexpr int kFaceArgs = 6 * 8 + (int)sizeof(GridDesc) + 2 * 8 + (int)sizeof(Scheme);  // through S
 
+// In FP64 held to three waves per SIMD (168 registers): the GKS second stage needs 169 left to itself and
+// then runs two; at 167 it spills 12 bytes (4096^2, two steps: 17.8 -> 17.3 ms; 512^2 1.2 % faster).  The
+// LF kernels take 136 to 156.
 template <class real, int FLUX, int OUT, int TF, int TR>
-__global__ __launch_bounds__(TF * (TR + 4)) void k_faces(const real* __restrict__ Wall, const real* __restrict__ Aall,
+__global__ __launch_bounds__(TF * (TR + 4), sizeof(real) == 8 ? 3 : 1) void k_faces(const real* __restrict__ Wall, const real* __restrict__ Aall,
                                                          real* __restrict__ FXall, real* __restrict__ FYall,
                                                          Ctrl* __restrict__ ctrls, GridDesc G0,
                                                          const GridDesc* __restrict__ grids,
