@@ -777,7 +777,7 @@ static dfw_status run_ckpt_impl(real* W, real* A, const dfw_grid* g, const dfw_p
   hipError_t he = hipSuccess;
   enqueue_steps<real>(W, A, (real*)(ws + L.ws_off), (real*)(ws + L.r_off), (real*)(ws + L.fx_off),
                       (real*)(ws + L.fy_off), ctrl, 1, G, nullptr, nullptr, shape_tiles(p->tile, g->nx, g->ny),
-                      nullptr, (int)cell_blocks(G), p, nsteps, dt_hist, st, [&](int n) {
+                      nullptr, (int)cell_blocks(G), p, nsteps, 0, nsteps, dt_hist, st, [&](int n) {
                         if (he == hipSuccess) he = hook(n);
                       });
   if (he == hipSuccess && C.tape && nsteps > 0) he = record(nsteps - 1);

@@ -1034,8 +1034,9 @@ static GridDesc make_desc(const dfw_grid* g) {
 
 static unsigned cell_blocks(const GridDesc& G) { return (unsigned)(((size_t)G.nx * G.ny + kCellBlock - 1) / kCellBlock); }
 
-// The kernels of nsteps time steps (S2O4, or SSP-RK3) on `st` (no synchronisation).  Single grid: grids/tiles/cblocks
-// are null and G0 describes the grid; batch: the tables describe every grid.
+// The kernels of steps [n0, n1) of nsteps time steps (S2O4, or SSP-RK3) on `st` (no synchronisation); the
+// control blocks are set up before step 0.  Single grid: grids/tiles/cblocks are null and G0 describes the
+// grid; batch: the tables describe every grid.
 struct NoHook {
   void operator()(int) const {}
 };
@@ -1044,8 +1045,8 @@ struct NoHook {
 template <class real, class Hook = NoHook>
 static void enqueue_steps(real* W, real* A, real* Ws, real* R, real* FX, real* FY, Ctrl* ctrls, int nctrl,
                           const GridDesc& G0, const GridDesc* grids, const int4* tiles, int ntiles,
-                          const int2* cblocks, int ncblocks, const dfw_params* p, int nsteps, double* dt_hist,
-                          hipStream_t st, Hook before_step = Hook()) {
+                          const int2* cblocks, int ncblocks, const dfw_params* p, int nsteps, int n0, int n1,
+                          double* dt_hist, hipStream_t st, Hook before_step = Hook()) {
   const Scheme S = make_scheme(p);
   FaceLaunch L;
   L.shape = p->tile;
@@ -1059,12 +1060,14 @@ static void enqueue_steps(real* W, real* A, real* Ws, real* R, real* FX, real* F
   const double dt_first = p->dt_fixed > 0 ? p->dt_fixed : 0.0;  // later launches of a step read ctrl->dt
   L.nsteps = nsteps;
   const unsigned nb = (unsigned)ncblocks;
-  hipLaunchKernelGGL(k_ctrl_init, dim3((nctrl + 63) / 64), dim3(64), 0, st, ctrls, nctrl);
-  timed(DFW_K_SPEED, st, [&] {
-    hipLaunchKernelGGL(k_speed<real>, dim3(nb), dim3(kCellBlock), 0, st, W, ctrls, G0, grids, cblocks, S, 0);
-  });
+  if (n0 == 0) {
+    hipLaunchKernelGGL(k_ctrl_init, dim3((nctrl + 63) / 64), dim3(64), 0, st, ctrls, nctrl);
+    timed(DFW_K_SPEED, st, [&] {
+      hipLaunchKernelGGL(k_speed<real>, dim3(nb), dim3(kCellBlock), 0, st, W, ctrls, G0, grids, cblocks, S, 0);
+    });
+  }
   if (S.ts == DFW_TIME_SSPRK3) {
-    for (int n = 0; n < nsteps; ++n) {
+    for (int n = n0; n < n1; ++n) {
       before_step(n);
       L.step = n;
       L.out = OUT_F | (S.dfs ? OUT_DF : 0);
@@ -1094,7 +1097,7 @@ static void enqueue_steps(real* W, real* A, real* Ws, real* R, real* FX, real* F
     }
     return;
   }
-  for (int n = 0; n < nsteps; ++n) {
+  for (int n = n0; n < n1; ++n) {
     before_step(n);
     L.step = n;
     L.out = OUT_F | OUT_FT | (S.tl ? OUT_OMEGA : 0) | (S.dfs ? OUT_DF : 0);
@@ -1127,7 +1130,7 @@ static dfw_status run_impl(real* W, real* A, const dfw_grid* g, const dfw_params
   const GridDesc G = make_desc(g);
   enqueue_steps<real>(W, A, (real*)(ws + L.ws_off), (real*)(ws + L.r_off), (real*)(ws + L.fx_off),
                       (real*)(ws + L.fy_off), ctrl, 1, G, nullptr, nullptr, shape_tiles(p->tile, g->nx, g->ny),
-                      nullptr, (int)cell_blocks(G), p, nsteps, dt_hist, st);
+                      nullptr, (int)cell_blocks(G), p, nsteps, 0, nsteps, dt_hist, st);
   HIP_TRY(hipGetLastError());
   Ctrl h;
   HIP_TRY(hipMemcpyAsync(&h, ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
@@ -1159,10 +1162,13 @@ struct dfw_batch {
   dfw::GridDesc* d_grids = nullptr;
   int4* d_tiles = nullptr;
   int2* d_cblocks = nullptr;
-  // captured rollout
-  hipGraphExec_t exec = nullptr;
-  hipGraph_t graph = nullptr;
+  // captured rollout, one graph per chunk of steps
+  std::vector<hipGraphExec_t> execs;
+  std::vector<hipGraph_t> graphs;
   hipStream_t cap_stream = nullptr;
+  // runs to a final time: whether grids are left to advance after a chunk (pinned, written by the device)
+  int* running = nullptr;
+  hipEvent_t chunk_done[2] = {nullptr, nullptr};
   void *g_W = nullptr, *g_A = nullptr, *g_ws = nullptr, *g_dth = nullptr;
   int g_nsteps = -1;
 };
@@ -1207,19 +1213,77 @@ static void build_tiles(dfw_batch* b, int order) {
   for (int w = 0; w < n; ++w) b->tiles[w] = list[xcd_tile(w, n)];
 }
 
+// With t_end the step count is an upper bound (the robustness sweeps allow four times the steps the initial
+// speed needs), and the launches past the last grid's end do nothing but take their time, about 2.3 us
+// each.  So such a run goes in chunks of kChunkSteps, the next one queued before the result of the one
+// before is looked at, and ends when no grid is left to advance: 16 tubes of 100 cells with SSP-RK3, 73
+// steps of at most 455.
+constexpr int kChunkSteps = 16;
+
+__global__ __launch_bounds__(256) void k_batch_running(const Ctrl* __restrict__ ctrls, int n, double t_end,
+                                                       int* __restrict__ running) {
+  int any = 0;
+  for (int g = threadIdx.x; g < n; g += 256) any |= ctrls[g].fail_at == kNoFail && ctrls[g].t < t_end;
+  any = __syncthreads_or(any);
+  if (threadIdx.x == 0) *running = any;
+}
+
+// The time steps of the steps [from, nsteps) that were not launched: 0, as a skipped step records it.
+__global__ __launch_bounds__(256) void k_dt_rest(const Ctrl* __restrict__ ctrls, double* __restrict__ dt_hist, int nsteps,
+                                                 int from) {
+  const int g = blockIdx.x;
+  if (ctrls[g].fail_at != kNoFail) return;
+  for (int n = from + (int)threadIdx.x; n < nsteps; n += 256) dt_hist[(size_t)g * nsteps + n] = 0.0;
+}
+
 template <class real>
-static void batch_enqueue(dfw_batch* b, void* W, void* A, char* ws, int nsteps, double* dth, hipStream_t st) {
+static void batch_enqueue_t(dfw_batch* b, void* W, void* A, char* ws, int nsteps, int n0, int n1, double* dth,
+                            hipStream_t st) {
   enqueue_steps<real>((real*)W, (real*)A, (real*)(ws + b->ws_off), (real*)(ws + b->r_off), (real*)(ws + b->fx_off),
                       (real*)(ws + b->fy_off), (Ctrl*)(ws + b->ctrl_off), b->ngrids, b->grids[0], b->d_grids,
-                      b->d_tiles, (int)b->tiles.size(), b->d_cblocks, (int)b->cblocks.size(), &b->params, nsteps, dth,
-                      st);
+                      b->d_tiles, (int)b->tiles.size(), b->d_cblocks, (int)b->cblocks.size(), &b->params, nsteps, n0,
+                      n1, dth, st);
+}
+
+// Steps [n0, n1), and with a non-null `running` the test whether grids are left to advance.
+static void batch_enqueue(dfw_batch* b, void* W, void* A, char* ws, int nsteps, int n0, int n1, double* dth,
+                          int* running, hipStream_t st) {
+  if (b->dtype == DFW_F64) batch_enqueue_t<double>(b, W, A, ws, nsteps, n0, n1, dth, st);
+  else batch_enqueue_t<float>(b, W, A, ws, nsteps, n0, n1, dth, st);
+  if (running)
+    hipLaunchKernelGGL(k_batch_running, dim3(1), dim3(256), 0, st, (const Ctrl*)(ws + b->ctrl_off), b->ngrids,
+                       b->params.t_end, running);
 }
 
 static void drop_graph(dfw_batch* b) {
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  b->exec = nullptr;
-  b->graph = nullptr;
+  for (hipGraphExec_t e : b->execs)
+    if (e) (void)hipGraphExecDestroy(e);
+  for (hipGraph_t g : b->graphs)
+    if (g) (void)hipGraphDestroy(g);
+  b->execs.clear();
+  b->graphs.clear();
+}
+
+// Captures and instantiates the next chunk's graph.  On an error the caller drops what is captured.
+static dfw_status batch_capture(dfw_batch* b, void* W, void* A, char* ws, int nsteps, int n0, int n1, double* dth,
+                                int* running) {
+  if (!b->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
+  HIP_TRY(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
+  const bool prof = g_prof.on;
+  g_prof.on = false;  // no events inside the graph
+  batch_enqueue(b, W, A, ws, nsteps, n0, n1, dth, running, b->cap_stream);
+  g_prof.on = prof;
+  hipError_t le = hipGetLastError();
+  hipGraph_t graph = nullptr;
+  hipError_t ce = hipStreamEndCapture(b->cap_stream, &graph);
+  if (graph) b->graphs.push_back(graph);
+  if (le != hipSuccess || ce != hipSuccess)
+    return fail(DFW_EHIP, std::string("graph capture failed: ") + hipGetErrorString(le != hipSuccess ? le : ce));
+  hipGraphExec_t exec = nullptr;
+  const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+  if (ie != hipSuccess) return fail(DFW_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
+  b->execs.push_back(exec);
+  return DFW_OK;
 }
 
 }  // namespace dfw
@@ -1498,37 +1562,53 @@ dfw_status dfw_batch_run(dfw_batch* b, void* W_flat, void* alpha_flat, int32_t n
   if (ws_bytes < b->ws_bytes) return fail(DFW_EWORKSPACE, "workspace too small: need " + std::to_string(b->ws_bytes));
   hipStream_t st = (hipStream_t)stream;
   if (use_graph) {
-    const bool same = b->exec && b->g_W == W_flat && b->g_A == alpha_flat && b->g_ws == ws &&
+    const bool same = !b->execs.empty() && b->g_W == W_flat && b->g_A == alpha_flat && b->g_ws == ws &&
                       b->g_dth == (void*)dt_hist_dev && b->g_nsteps == nsteps;
     if (!same) {
       drop_graph(b);
-      if (!b->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
-      HIP_TRY(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-      const bool prof = g_prof.on;
-      g_prof.on = false;  // no events inside the graph
-      if (b->dtype == DFW_F64) batch_enqueue<double>(b, W_flat, alpha_flat, (char*)ws, nsteps, dt_hist_dev, b->cap_stream);
-      else batch_enqueue<float>(b, W_flat, alpha_flat, (char*)ws, nsteps, dt_hist_dev, b->cap_stream);
-      g_prof.on = prof;
-      hipError_t le = hipGetLastError();
-      hipError_t ce = hipStreamEndCapture(b->cap_stream, &b->graph);
-      if (le != hipSuccess || ce != hipSuccess) {
-        drop_graph(b);
-        return fail(DFW_EHIP, std::string("graph capture failed: ") + hipGetErrorString(le != hipSuccess ? le : ce));
-      }
-      HIP_TRY(hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
       b->g_W = W_flat;
       b->g_A = alpha_flat;
       b->g_ws = ws;
       b->g_dth = (void*)dt_hist_dev;
       b->g_nsteps = nsteps;
     }
-    hipError_t ge = hipSuccess;
-    timed(DFW_K_GRAPH, st, [&] { ge = hipGraphLaunch(b->exec, st); });
-    HIP_TRY(ge);
-  } else {
-    if (b->dtype == DFW_F64) batch_enqueue<double>(b, W_flat, alpha_flat, (char*)ws, nsteps, dt_hist_dev, st);
-    else batch_enqueue<float>(b, W_flat, alpha_flat, (char*)ws, nsteps, dt_hist_dev, st);
   }
+  const bool chunked = b->params.t_end > 0.0 && nsteps > kChunkSteps;
+  if (chunked && !b->running) {
+    HIP_TRY(hipEventCreateWithFlags(&b->chunk_done[0], hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&b->chunk_done[1], hipEventDisableTiming));
+    HIP_TRY(hipHostMalloc((void**)&b->running, 2 * sizeof(int), hipHostMallocDefault));
+  }
+  const int chunk = chunked ? kChunkSteps : nsteps;
+  int done = 0;
+  for (int c = 0; c == 0 || done < nsteps; ++c) {
+    if (c >= 2) {  // the chunk before the one in flight
+      HIP_TRY(hipEventSynchronize(b->chunk_done[c & 1]));
+      if (!*(volatile int*)&b->running[c & 1]) break;
+    }
+    const int n1 = std::min(nsteps, done + chunk);
+    int* running = chunked ? b->running + (c & 1) : nullptr;
+    if (use_graph) {
+      if ((size_t)c == b->execs.size()) {
+        const dfw_status cs = batch_capture(b, W_flat, alpha_flat, (char*)ws, nsteps, done, n1, dt_hist_dev, running);
+        if (cs != DFW_OK) {
+          (void)hipStreamSynchronize(st);  // chunks before this one may be running
+          drop_graph(b);
+          return cs;
+        }
+      }
+      hipError_t ge = hipSuccess;
+      timed(DFW_K_GRAPH, st, [&] { ge = hipGraphLaunch(b->execs[c], st); });
+      HIP_TRY(ge);
+    } else {
+      batch_enqueue(b, W_flat, alpha_flat, (char*)ws, nsteps, done, n1, dt_hist_dev, running, st);
+    }
+    if (chunked) HIP_TRY(hipEventRecord(b->chunk_done[c & 1], st));
+    done = n1;
+  }
+  if (done < nsteps && dt_hist_dev)
+    hipLaunchKernelGGL(k_dt_rest, dim3(b->ngrids), dim3(256), 0, st, (const Ctrl*)((char*)ws + b->ctrl_off), dt_hist_dev,
+                       nsteps, done);
   HIP_TRY(hipGetLastError());
   std::vector<Ctrl> h(b->ngrids);
   HIP_TRY(hipMemcpyAsync(h.data(), (char*)ws + b->ctrl_off, b->ngrids * sizeof(Ctrl), hipMemcpyDeviceToHost, st));
@@ -1547,6 +1627,9 @@ void dfw_batch_free(dfw_batch* b) {
   if (!b) return;
   drop_graph(b);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+  for (hipEvent_t e : b->chunk_done)
+    if (e) (void)hipEventDestroy(e);
+  if (b->running) (void)hipHostFree(b->running);
   if (b->dtab) (void)hipFree(b->dtab);
   delete b;
 }
