@@ -9,7 +9,7 @@
 //                 the seed terms of the cells beside its interfaces (formed once per cell),
 //                 recomputes the normal-sweep line values of TR+8 rows, runs the segment adjoint
 //                 (Gauss-point reconstruction, flux, DF) of TR+4 segment rows, sums for each row the
-//                 line adjoints of the five segments that read it (five LDS rounds in a fixed order),
+//                 line adjoints of the five segments that read it (from LDS, in a fixed order),
 //                 runs the normal-sweep adjoint of the rows the tile owns, and writes per row the
 //                 adjoints of the seven cells its two interfaces' normal stencils cover and of the
 //                 three DFs they read, the two interfaces' terms summed in the tile: 31 values, each
@@ -576,32 +576,81 @@ __device__ __forceinline__ Preimages preimages(int n, int Nn, int bc, int lo, in
   return p;
 }
 
-// Sum of the window-buffer entries of one direction that belong to cell (n, t) (normal, tangential
-// index).  The window of tile k (interfaces 2k and 2k+1) and row `row` holds, at slot w*4 + c, the
-// adjoint of component c of cell 2k-3+w (w = 0..6), and at slot 28 + d that of the DF of cell
-// 2k-1+d (d = 0..2); it sits at B[slot*sB + k*fs + (row+2)*rs].  A cell is in the windows of three or
-// four tiles (its DF in one or two), summed in increasing k.
+// The window-buffer entries of one direction that belong to cell e (normal index, ghost cells
+// included) of one row.  The window of tile k (interfaces 2k and 2k+1) and row `row` holds, at slot
+// w*4 + c, the adjoint of component c of cell 2k-3+w (w = 0..6), and at slot 28 + d that of the DF of
+// cell 2k-1+d (d = 0..2); it sits at B[slot*sB + k*fs + (row+2)*rs].  A cell is in the windows of
+// three or four tiles (its DF in one or two), summed in increasing k.  All 18 loads are issued at
+// once, at a window of the cell where a tile is missing, and the sums leave those out.
 template <class real>
-__device__ __forceinline__ void gather_dir(const real* __restrict__ B, size_t sB, size_t fs, size_t rs, int n, int Nn,
-                                           int bcn, int t, int Nt, int bct, real* g, real& ga) {
-  const int nk = (Nn + 2) / 2;
-  const Preimages pt = preimages(t, Nt, bct, -2, Nt + 1);
-  const Preimages pn = preimages(n, Nn, bcn, -3, Nn + 2);
-  for (int tp = pt.first; tp <= pt.last; tp += pt.stride) {
-    const real* row = B + (size_t)(tp + 2) * rs;
-    for (int e = pn.first; e <= pn.last; e += pn.stride) {
-      const int k0 = max((e - 2) >> 1, 0), k1 = min((e + 3) >> 1, nk - 1);  // floor division
-      for (int kk = k0; kk <= k1; ++kk) {
-        const int w = e - 2 * kk + 3;
+struct WindowEntries {
+  real v[4][4], vd[2];
+  int nv, nd;  // entries of the cell and of its DF
+
+  __device__ __forceinline__ void load(const real* __restrict__ row, size_t sB, size_t fs, int nk, int e) {
+    const int k0 = max((e - 2) >> 1, 0), k1 = min((e + 3) >> 1, nk - 1);  // floor division
+    const int d0 = max(e >> 1, 0), d1 = min((e + 1) >> 1, nk - 1);
+    nv = k1 - k0 + 1;
+    nd = d1 - d0 + 1;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) g[c] += row[(w * 4 + c) * sB + kk * fs];
-      }
-      const int d0 = max(e >> 1, 0), d1 = min((e + 1) >> 1, nk - 1);
-      for (int kk = d0; kk <= d1; ++kk) ga += row[(28 + e - 2 * kk + 1) * sB + kk * fs];
+    for (int m = 0; m < 4; ++m) {
+      const int kk = min(k0 + m, k1), w = e - 2 * kk + 3;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[m][c] = row[(w * 4 + c) * sB + kk * fs];
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int kk = max(min(d0 + m, d1), 0), d = min(max(e - 2 * kk + 1, 0), 2);
+      vd[m] = row[(28 + d) * sB + kk * fs];
     }
   }
-}
 
+  __device__ __forceinline__ void add(real* g, real& ga) const {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) g[c] = m < nv ? g[c] + v[m][c] : g[c];
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) ga = m < nd ? ga + vd[m] : ga;
+  }
+};
+
+// One direction of the gather for cell (n, t) (normal, tangential index): the entries of the cell
+// itself or of the first ghost cell that folds back to it, then those of the others.
+template <class real>
+struct GatherDir {
+  const real* B;
+  size_t sB, fs, rs;
+  int nk;
+  Preimages pt, pn;
+  WindowEntries<real> first;
+
+  __device__ __forceinline__ GatherDir(const real* __restrict__ B_, size_t sB_, size_t fs_, size_t rs_, int n, int Nn,
+                                       int bcn, int t, int Nt, int bct)
+      : B(B_), sB(sB_), fs(fs_), rs(rs_), nk((Nn + 2) / 2) {
+    pt = preimages(t, Nt, bct, -2, Nt + 1);
+    pn = preimages(n, Nn, bcn, -3, Nn + 2);
+    first.load(B + (size_t)(pt.first + 2) * rs, sB, fs, nk, pn.first);
+  }
+
+  __device__ __forceinline__ void add(real* g, real& ga) const {
+    first.add(g, ga);
+    for (int tp = pt.first; tp <= pt.last; tp += pt.stride)
+      for (int e = pn.first + (tp == pt.first ? pn.stride : 0); e <= pn.last; e += pn.stride) {
+        WindowEntries<real> w;
+        w.load(B + (size_t)(tp + 2) * rs, sB, fs, nk, e);
+        w.add(g, ga);
+      }
+  }
+};
+
+// Bound by HBM on large grids (1024^2: 0.08 ms, 4.3-4.6 TB/s) and by the latency of its loads on small
+// ones, where a loop over the tiles of each direction waited for memory about eleven times in turn.
+// Both directions' entries are now in flight together, one wait for a cell away from the periodic
+// border: 192 x 160, GKS, four steps and their gradient 1.08 -> 1.00 ms; 1024^2 0.5 % faster.
+// Workgroups of 64 or 128 threads, which reach more compute units on a small grid, gained nothing
+// more there and cost 0.7-1.2 % of the gradient at 1024^2.
 // STAGE 2: LWs = adjoint of W* (from the stage-2 interfaces), LA = stage-2 part of the adjoint of
 //          alpha^n.
 // STAGE 1: LW <- LW + LWs + stage-1 part (adjoint of W^n), LA <- LA + stage-1 part.
@@ -612,11 +661,14 @@ __global__ __launch_bounds__(kCellBlock) void k_adj_gather(const real* __restric
   const int nx = G.nx, ny = G.ny;
   const size_t N = (size_t)nx * ny, o = (size_t)blockIdx.x * kCellBlock + threadIdx.x;
   if (o >= N) return;
-  const int i = (int)(o % nx), j = (int)(o / nx);
+  // 32 bits hold the cell index: at 2^32 cells the two window buffers alone would take 1 TB.
+  const int j = (int)((unsigned)o / (unsigned)nx), i = (int)((unsigned)o - (unsigned)j * (unsigned)nx);
   real g[4] = {0, 0, 0, 0}, ga = 0;
   const size_t nkx = (size_t)(nx + 2) / 2, nky = (size_t)(ny + 2) / 2;
-  gather_dir(BX, (size_t)(ny + 4) * nkx, 1, nkx, i, nx, G.bc_x, j, ny, G.bc_y, g, ga);
-  gather_dir(BY, nky * (nx + 4), (size_t)nx + 4, 1, j, ny, G.bc_y, i, nx, G.bc_x, g, ga);
+  const GatherDir<real> dx(BX, (size_t)(ny + 4) * nkx, 1, nkx, i, nx, G.bc_x, j, ny, G.bc_y);
+  const GatherDir<real> dy(BY, nky * (nx + 4), (size_t)nx + 4, 1, j, ny, G.bc_y, i, nx, G.bc_x);
+  dx.add(g, ga);
+  dy.add(g, ga);
   if (STAGE == 2) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) LWs[c * N + o] = g[c];
