@@ -61,7 +61,7 @@ typedef struct {
  *   c1, c2       numerical collision time tau_n = c1 dt + c2 |(pl-pr)/(pl+pr)| dt (Section 2.2) [0.01, 5]
  *   flux         DFW_FLUX_LF or DFW_FLUX_GKS
  *   tile         interface tile shape, 0 <= tile < dfw_num_tiles() [0]; results do not depend on it.
- *                0 leaves the choice to the library, which takes the shape of index 0, 3 or 4 by
+ *                0 leaves the choice to the library, which takes the shape of index 3, 4 or 5 by
  *                the size of the call
  *   time_limiter 1: the non-linear time limiter of Section 2.2 (eqs. (27)-(29)) for the second-stage
  *                update; 0: plain eq. (21) [0].  The limiter's epsilon is eps_weno.  dfw_rhs
@@ -225,7 +225,8 @@ dfw_status dfw_adjoint(const dfw_grid* grid, const dfw_params* params, int32_t d
                        const void* gW_final, const void* gA_final, void* gW0, void* gA0, void* ws, size_t ws_bytes,
                        void* stream);
 
-/* Interface tile shapes available for dfw_params.tile: TF interfaces by TR segments. */
+/* Interface tile shapes available for dfw_params.tile: TF interfaces by TR segments; 0 by 0 for index 0,
+ * which leaves the choice to the library. */
 int32_t dfw_num_tiles(void);
 dfw_status dfw_tile_shape(int32_t tile, int32_t* tf, int32_t* tr);
 

@@ -52,7 +52,8 @@ class Params:
 
 
 def tile_shapes():
-    """[(TF, TR)] of the interface tile shapes the library provides (index = Params.tile)."""
+    """[(TF, TR)] of the interface tile shapes the library provides (index = Params.tile); (0, 0) at index 0,
+    which leaves the choice to the library."""
     L = _lib.load()
     out = []
     for k in range(L.dfw_num_tiles()):

@@ -45,6 +45,11 @@ def _key(kind, sizes, dtype, params: api.Params) -> str:
     return f"{kind}|{_arch()}|hip{torch.version.hip}|{str(dtype).split('.')[-1]}|flux{params.flux}|{h}"
 
 
+def _tiles():
+    """The candidates: every shape by its own index (index 0 would time one of them a second time)."""
+    return [k for k, shape in enumerate(api.tile_shapes()) if shape != (0, 0)]
+
+
 def _load() -> dict:
     try:
         with open(cache_path()) as f:
@@ -89,7 +94,7 @@ def tune_batch(grids, Ws, alphas, params: api.Params, dtype=torch.float64, steps
         if hit:
             return hit["tile"], hit["order"], hit["timings"]
     timings = {}
-    for tile in range(len(api.tile_shapes())):
+    for tile in _tiles():
         p = api.Params(**{**params.__dict__, "tile": tile})
         for order in ORDERS:
             timings[f"{tile},{order}"] = _time_batch(grids, Ws, alphas, p, dtype, order, steps, reps)
@@ -109,7 +114,7 @@ def tune_grid(prob, params: api.Params, dtype=torch.float64, steps=5, reps=2, us
     W0 = torch.tensor(prob.W, dtype=dtype, device="cuda")
     A0 = torch.tensor(prob.alpha, dtype=dtype, device="cuda")
     timings = {}
-    for tile in range(len(api.tile_shapes())):
+    for tile in _tiles():
         p = api.Params(**{**params.__dict__, "tile": tile})
         st = api.Stepper.for_problem(prob, p, dtype)
         W, A = W0.clone(), A0.clone()

@@ -794,12 +794,13 @@ static void timed(int kind, hipStream_t st, Launch launch) {
   if (ok_a && ok_b) g_prof.recs.push_back({kind, a, b});  // a launch without both events is not timed
 }
 
-// Interface tile shapes (TF interfaces x TR segments); index 0 leaves the choice to the library
-// (default_shape: this shape, or another that suits the launch's size).
+// Interface tile shapes (TF interfaces x TR segments); index 0 is no shape of its own, it leaves the
+// choice to the library (default_shape).
 struct TileShape {
   int tf, tr;
 };
-static const TileShape kShapes[] = {{8, 28}, {16, 28}, {8, 60}, {16, 12}, {4, 60}};
+static const TileShape kShapes[] = {{0, 0}, {16, 28}, {8, 60}, {16, 12}, {4, 60}, {8, 28}};
+enum { kShape16x12 = 3, kShape4x60 = 4, kShape8x28 = 5 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 static int compute_units() {
@@ -814,7 +815,7 @@ static int compute_units() {
   return n;
 }
 
-// The shape behind tile index 0, from the number of tiles n0, n3, n4 that the 8x28, 16x12 and 4x60 shapes
+// The shape behind tile index 0, from the number of tiles n5, n3, n4 that the 8x28, 16x12 and 4x60 shapes
 // (256 threads each) need for the whole launch.  Results do not depend on it.  Measured, us per LF step in
 // FP64 unless noted, 8x28 / 16x12 / 4x60:
 //   a tile per compute unit or less (n3 <= units): the short 16x12 tile has the shortest way from its
@@ -826,12 +827,12 @@ static int compute_units() {
 //     4 % of the tiles: 2048^2 1734 / 1897 / 1670, 4096^2 in FP32 5509 / 6143 / 5226, 1001x750 GKS in
 //     FP32 447 / 495 / 428 (1024^2, where it saves 3 %: 452 / 494 / 465);
 //   in between 8x28, which stages less: 512^2 133 / 153 / 135, GKS 174 / 205 / 178.
-static int default_shape(long long n0, long long n3, long long n4) {
+static int default_shape(long long n5, long long n3, long long n4) {
   const long long units = compute_units();
-  if (n3 <= units) return 3;
-  if (n0 <= 4 * units) return n4 <= n0 ? 4 : 0;
-  if (n0 >= 24 * units) return 25 * n4 <= 24 * n0 ? 4 : 0;
-  return 0;
+  if (n3 <= units) return kShape16x12;
+  if (n5 <= 4 * units) return n4 <= n5 ? kShape4x60 : kShape8x28;
+  if (n5 >= 24 * units) return 25 * n4 <= 24 * n5 ? kShape4x60 : kShape8x28;
+  return kShape8x28;
 }
 
 static int shape_tiles(int shape, int nx, int ny) {
@@ -843,13 +844,13 @@ static int shape_tiles(int shape, int nx, int ny) {
 static dfw_params with_shape(const dfw_params* p, const dfw_grid* grids, int n) {
   dfw_params q = *p;
   if (q.tile == 0) {
-    long long n0 = 0, n3 = 0, n4 = 0;
+    long long n3 = 0, n4 = 0, n5 = 0;
     for (int g = 0; g < n; ++g) {
-      n0 += shape_tiles(0, grids[g].nx, grids[g].ny);
-      n3 += shape_tiles(3, grids[g].nx, grids[g].ny);
-      n4 += shape_tiles(4, grids[g].nx, grids[g].ny);
+      n3 += shape_tiles(kShape16x12, grids[g].nx, grids[g].ny);
+      n4 += shape_tiles(kShape4x60, grids[g].nx, grids[g].ny);
+      n5 += shape_tiles(kShape8x28, grids[g].nx, grids[g].ny);
     }
-    q.tile = default_shape(n0, n3, n4);
+    q.tile = default_shape(n5, n3, n4);
   }
   return q;
 }
@@ -878,8 +879,8 @@ static void launch_faces_shape(const FaceLaunch& L, const real* W, const real* A
   switch (L.shape) {
     case 1: launch_faces_t<real, FLUX, OUT, 16, 28>(L, W, A, FX, FY, st); break;
     case 2: launch_faces_t<real, FLUX, OUT, 8, 60>(L, W, A, FX, FY, st); break;
-    case 3: launch_faces_t<real, FLUX, OUT, 16, 12>(L, W, A, FX, FY, st); break;
-    case 4: launch_faces_t<real, FLUX, OUT, 4, 60>(L, W, A, FX, FY, st); break;
+    case kShape16x12: launch_faces_t<real, FLUX, OUT, 16, 12>(L, W, A, FX, FY, st); break;
+    case kShape4x60: launch_faces_t<real, FLUX, OUT, 4, 60>(L, W, A, FX, FY, st); break;
     default: launch_faces_t<real, FLUX, OUT, 8, 28>(L, W, A, FX, FY, st); break;
   }
 }
