@@ -146,6 +146,22 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int n) {
   return x * q + (x < r ? x : r) + k;
 }
 
+// Whether x holds in any lane of the wave (the same in every lane).
+__device__ __forceinline__ bool wave_any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
+
+// x, or in a wave where it holds in some lanes but in fewer than half of them, true.
+__device__ __forceinline__ bool or_few(bool x) {
+  const unsigned long long m = __builtin_amdgcn_ballot_w64(x);
+  return x || (m != 0 && __builtin_popcountll(m) < 32);
+}
+
+// Four values that every active lane computes, whether or not it uses them.
+template <class real>
+__device__ __forceinline__ void pin_values(real* x) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(x[c]));
+}
+
 // A value the same in every lane, moved to scalar registers (kernels at the register limit would
 // otherwise hold values computed by vector instructions in vector registers).
 __device__ __forceinline__ double uniform_value(double x) {
@@ -185,11 +201,15 @@ __host__ __device__ inline int tiles_x(int nx, int ny) { return ((nx + 1 + TF - 
 
 constexpr int kFaceArgs = 6 * 8 + (int)sizeof(GridDesc) + 2 * 8 + (int)sizeof(Scheme);  // through S
 
-// In FP64 held to three waves per SIMD (168 registers): the GKS second stage needs 169 left to itself and
-// then runs two; at 167 it spills 12 bytes (4096^2, two steps: 17.8 -> 17.3 ms; 512^2 1.2 % faster).  The
-// LF kernels take 136 to 156.
+// In FP64 held to three waves per SIMD (168 registers): the GKS second stage needs more left to itself and
+// then runs two (4096^2, two steps: 17.8 -> 17.3 ms; 512^2 1.2 % faster).  It takes 167 without spills, with
+// the time limiter 168 and 12 bytes of scratch; the LF kernels take 136 to 158.  GKS in FP32 is held to
+// five waves (96 registers; 97 to 105 left to itself, four waves: 1001x750 1.70 -> 1.68 ms for four steps).
+constexpr int faces_waves(size_t element, int flux) { return element == 8 ? 3 : (flux == DFW_FLUX_GKS ? 5 : 1); }
+
 template <class real, int FLUX, int OUT, int TF, int TR>
-__global__ __launch_bounds__(TF * (TR + 4), sizeof(real) == 8 ? 3 : 1) void k_faces(const real* __restrict__ Wall, const real* __restrict__ Aall,
+__global__ __launch_bounds__(TF * (TR + 4), faces_waves(sizeof(real), FLUX)) void k_faces(const real* __restrict__ Wall,
+                                                         const real* __restrict__ Aall,
                                                          real* __restrict__ FXall, real* __restrict__ FYall,
                                                          Ctrl* __restrict__ ctrls, GridDesc G0,
                                                          const GridDesc* __restrict__ grids,
@@ -337,7 +357,13 @@ __global__ __launch_bounds__(TF * (TR + 4), sizeof(real) == 8 ? 3 : 1) void k_fa
   }
   const int rstride = dir == 0 ? TF : 1;  // thread-index distance between neighbouring rows
   const int f = f0 + fl, t = t0 - 2 + rr;
-  const bool live1 = f <= Nn && t < Nt + 2;
+  // The sweeps run on every lane of a wave that holds a live item: the lanes past the end of a ragged
+  // tile work on their own staged (boundary-mapped) cells and store nothing.  A wave of few active lanes
+  // takes more cycles for the same instructions (LF, FP64: 19 400 with 48 lanes, 23 000 with 24, 43 800
+  // with 8), and one such tile is then the length of a small launch.  us per step on 8x28 tiles before and
+  // with it: 24 x 24 LF in FP64 42 / 30, GKS in FP64 53 / 35, in FP32 70 / 37; 256 x 256 GKS in FP64 87 / 66;
+  // 80 x 80 and 512 x 512, whose last tiles are fuller, the same.
+  const bool live1 = wave_any(f <= Nn && t < Nt + 2);
   real wln[4] = {0, 0, 0, 0}, wrn[4] = {0, 0, 0, 0};
   real om = real(1);  // time-limiter weight of this interface segment, from the normal sweep
   real* const omp = (OUT & OUT_OMEGA) ? &om : nullptr;
@@ -376,13 +402,16 @@ __global__ __launch_bounds__(TF * (TR + 4), sizeof(real) == 8 ? 3 : 1) void k_fa
 
   // ---- tangential sweep at the Gauss points, fluxes, DF
   const bool live2 = f <= Nn && rr >= 2 && rr < TR + 2 && t < Nt;
-  if (!live2) return;
+  if (!or_few(live2)) return;
+  // the row whose segment a lane works on: its own, or for a lane without one the nearest that has all
+  // five line values
+  const int rs = min(max(rr, 2), min(TR + 1, Nt + 1 - t0)), ls = tid + (rs - rr) * rstride;
   real al[2][3];
 #pragma unroll
   for (int side = 0; side < 2; ++side)  // DF of the cell on the same side as the Gauss point
 #pragma unroll
-    for (int q = 0; q < 3; ++q) al[side][q] = sA[rr - 1 + q][fl + 1 + side];
-  auto line = [&](int side, int m, int c) -> real { return sLine[4 * side + c][tid + (m - 2) * rstride]; };
+    for (int q = 0; q < 3; ++q) al[side][q] = sA[rs - 1 + q][fl + 1 + side];
+  auto line = [&](int side, int m, int c) -> real { return sLine[4 * side + c][ls + (m - 2) * rstride]; };
   real Fs[4], Fts[4], dfp;
   constexpr bool kF = (OUT & OUT_F) != 0, kDF = (OUT & OUT_DF) != 0;
   if constexpr (kF32) {
@@ -405,6 +434,15 @@ __global__ __launch_bounds__(TF * (TR + 4), sizeof(real) == 8 ? 3 : 1) void k_fa
     segment_point_fluxes<FLUX, kF, kDF>(gw, gwt, wln, wrn, dt, k, Fs, Fts, dfp);
   }
   // ---- write face sums (quadrature weights 1/2), components back to the global order
+  // (pinned, else the compiler moves their computation behind the test, back to the few lanes: 24 x 24 GKS in
+  // FP64 43 us per step without, 35 with; the FP32 LF kernels stay as they are without it, and with it
+  // 4096^2 ran 0.6 % slower)
+  if constexpr (FLUX == DFW_FLUX_GKS || !kF32) {
+    if constexpr (kF) pin_values(Fs);
+    if constexpr ((OUT & OUT_FT) != 0) pin_values(Fts);
+    if constexpr (kDF) asm volatile("" : "+v"(dfp));
+  }
+  if (!live2) return;
   const size_t fstride = dir == 0 ? (size_t)ny * (nx + 1) : (size_t)(ny + 1) * nx;
   real* Fo = dir == 0 ? FX + (size_t)t * (nx + 1) + f : FY + (size_t)f * nx + t;
   const int cmap[4] = {0, dir ? 2 : 1, dir ? 1 : 2, 3};
