@@ -61,8 +61,8 @@ typedef struct {
  *   c1, c2       numerical collision time tau_n = c1 dt + c2 |(pl-pr)/(pl+pr)| dt (Section 2.2) [0.01, 5]
  *   flux         DFW_FLUX_LF or DFW_FLUX_GKS
  *   tile         interface tile shape, 0 <= tile < dfw_num_tiles() [0]; results do not depend on it.
- *                0 leaves the choice to the library, which takes the shape of index 3, 4 or 5 by
- *                the size of the call
+ *                0 leaves the choice to the library, which takes the shape of index 5, 4 or 3 by
+ *                the number of tiles per compute unit that the call needs with each
  *   time_limiter 1: the non-linear time limiter of Section 2.2 (eqs. (27)-(29)) for the second-stage
  *                update; 0: plain eq. (21) [0].  The limiter's epsilon is eps_weno.  dfw_rhs
  *                returns the unlimited dL/dt; dfw_adjoint rejects time_limiter = 1.

@@ -853,24 +853,31 @@ static int compute_units() {
   return n;
 }
 
-// The shape behind tile index 0, from the number of tiles n5, n3, n4 that the 8x28, 16x12 and 4x60 shapes
-// (256 threads each) need for the whole launch.  Results do not depend on it.  Measured, us per LF step in
-// FP64 unless noted, 8x28 / 16x12 / 4x60:
-//   a tile per compute unit or less (n3 <= units): the short 16x12 tile has the shortest way from its
-//     loads to its stores: 64^2 47 / 35 / 55, 100^2 34 / 33 / 34 (160^2, just above: 34 / 40 / 34);
-//   up to four 8x28 tiles per unit (all resident, or one round and a tail): the shape with fewer
-//     tiles: 200x150 57 / 44 / 45, 256^2 65 / 56 / 55, 300^2 72 / 70 / 62 (a batch of eight grids of 32 to
-//     128 cells, which needs more of the tall tiles: 357 / 349 / 411);
-//   from 24 per unit on the 4x60 tile, whose lanes idle less in the tangential phase, if it saves
-//     4 % of the tiles: 2048^2 1734 / 1897 / 1670, 4096^2 in FP32 5509 / 6143 / 5226, 1001x750 GKS in
-//     FP32 447 / 495 / 428 (1024^2, where it saves 3 %: 452 / 494 / 465);
-//   in between 8x28, which stages less: 512^2 133 / 153 / 135, GKS 174 / 205 / 178.
-static int default_shape(long long n5, long long n3, long long n4) {
+// The shape behind tile index 0, from the number of tiles n5, n4, n3 that the 8x28, 4x60 and 16x12 shapes
+// (256 threads each) need for the whole launch.  Results do not depend on it.  A launch takes as long as the
+// compute unit with the most tiles, so the count per unit, rounded up (c), decides.  us per step, GKS in
+// FP64 unless noted (LF, SSP-RK3, the time limiter and FP32 lie alike):
+//   equal c: the same time (64^2 35 / 36 / 35 for 8x28 / 4x60 / 16x12, 256^2 66 / 66 / 66, 400^2 119 / 120), and
+//     8x28 stages less (512^2 175 / 177; 16x12 with c = 12 against 10 there 198);
+//   4x60 where its c is 3 % smaller: 300^2, c 4 / 3, 92 / 78; 600^2, 14 / 12, 234 / 211; 1001x750, 27 / 26, 432 / 426,
+//     LF in FP32 267 / 268; 1200^2, 51 / 48, 792 / 757, LF in FP32 475 / 470.  At 1024^2, 38 / 37, LF in FP32
+//     takes 361 / 367 and GKS 592 / 585;
+//   16x12, which has the fewest tiles on thin grids, while they are few: 1500x9, c 2 / 1 for 8x28 / 16x12, 48 / 38;
+//     5000x10, 4 / 3, 80 / 68, in FP32 80 / 68.  It stages a third more rows: 20000x1, 13 / 12, 108 / 98, but in
+//     FP32 98 / 102.
+// Batches follow the same counts: 8 grids of 32 to 128 cells, c 3 / 2 for 8x28 / 4x60, ten steps 623 / 526 us; 48
+// of 32 to 256 cells, 36 / 37, 5.4 / 5.6 ms.
+static int default_shape(long long n5, long long n4, long long n3) {
   const long long units = compute_units();
-  if (n3 <= units) return kShape16x12;
-  if (n5 <= 4 * units) return n4 <= n5 ? kShape4x60 : kShape8x28;
-  if (n5 >= 24 * units) return 25 * n4 <= 24 * n5 ? kShape4x60 : kShape8x28;
-  return kShape8x28;
+  auto per_unit = [&](long long n) { return (n + units - 1) / units; };
+  int shape = kShape8x28;
+  long long c = per_unit(n5);
+  auto offer = [&](int s, long long cs) {
+    if (32 * cs <= 31 * c) shape = s, c = cs;
+  };
+  offer(kShape4x60, per_unit(n4));
+  if (c <= 4) offer(kShape16x12, per_unit(n3));
+  return shape;
 }
 
 static int shape_tiles(int shape, int nx, int ny) {
@@ -888,7 +895,7 @@ static dfw_params with_shape(const dfw_params* p, const dfw_grid* grids, int n) 
       n4 += shape_tiles(kShape4x60, grids[g].nx, grids[g].ny);
       n5 += shape_tiles(kShape8x28, grids[g].nx, grids[g].ny);
     }
-    q.tile = default_shape(n5, n3, n4);
+    q.tile = default_shape(n5, n4, n3);
   }
   return q;
 }
