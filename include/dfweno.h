@@ -154,8 +154,8 @@ dfw_status dfw_rhs(const void* W, const void* alpha, const dfw_grid* grid, const
 /* ---- Batched ragged grids ---------------------------------------------------------------------
  * Many independent grids (own sizes, spacing, boundaries and CFL time steps; one dfw_params for
  * all) advanced together: every kernel launch covers the interfaces or cells of all grids, and
- * dfw_batch_run can capture the whole nsteps rollout once into a hipGraph and replay it with one
- * launch.  The states are packed back to back: grid g's W ([4][ny_g][nx_g]) starts at element
+ * dfw_batch_run can capture the rollout into hipGraphs and replay them: one graph of all nsteps, or
+ * with t_end > 0 one for every 16 steps.  The states are packed back to back: grid g's W ([4][ny_g][nx_g]) starts at element
  * w_offsets[g] of W_flat and its alpha at a_offsets[g] of alpha_flat (dfw_batch_layout). */
 typedef struct dfw_batch dfw_batch;
 
@@ -171,8 +171,12 @@ dfw_status dfw_batch_plan(const dfw_grid* grids, int32_t ngrids, const dfw_param
 dfw_status dfw_batch_layout(const dfw_batch* b, int64_t* w_offsets, int64_t* a_offsets, size_t* w_elems,
                             size_t* a_elems, size_t* ws_bytes);
 
-/* Advances every grid by nsteps S2O4 steps in place.  use_graph != 0 replays a hipGraph captured
- * at the first call with these pointers and nsteps (re-captured when they change).
+/* Advances every grid by nsteps S2O4 steps in place.  use_graph != 0 replays hipGraphs captured at
+ * the first call with these pointers and nsteps (re-captured when they change).  With t_end > 0,
+ * where nsteps is an upper bound, the call goes in chunks of 16 steps, with use_graph = 0 too: it
+ * waits for each chunk once the next one is queued (a graph is captured when its chunk is first
+ * reached), and ends when no grid is left to advance; the time steps of steps that were not reached
+ * are recorded as 0.  Returns with the stream idle, on an error too.
  *   dt_hist_dev  device, optional: [ngrids][nsteps] FP64 time increments.
  *   t_out        host, optional: [ngrids] simulated time of each grid.
  *   fail_steps   host, optional: [ngrids] -1 or the completed steps when that grid met a
@@ -238,7 +242,7 @@ enum {
   DFW_K_FACES2 = 2,   /* interface kernel, second stage (time derivative and DF) */
   DFW_K_UPDATE2 = 3,  /* cell kernel, second stage (W^{n+1}, alpha^{n+1}, CFL reduction) */
   DFW_K_SPEED = 4,    /* standalone CFL reduction of the input state */
-  DFW_K_GRAPH = 5,    /* one replay of a captured batched rollout */
+  DFW_K_GRAPH = 5,    /* one replay of a captured batched rollout, or of one chunk of it (t_end > 0) */
   DFW_K_ADJ_FACES1 = 6, /* adjoint interface kernel, first stage */
   DFW_K_ADJ_FACES2 = 7, /* adjoint interface kernel, second stage */
   DFW_K_ADJ_GATHER = 8, /* adjoint cell gather (both stages) */

@@ -1310,7 +1310,7 @@ static void drop_graph(dfw_batch* b) {
   b->graphs.clear();
 }
 
-// Captures and instantiates the next chunk's graph.  On an error the caller drops what is captured.
+// Captures and instantiates the next chunk's graph.  On an error batch_rollout's caller drops what is captured.
 static dfw_status batch_capture(dfw_batch* b, void* W, void* A, char* ws, int nsteps, int n0, int n1, double* dth,
                                 int* running) {
   if (!b->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
@@ -1329,6 +1329,46 @@ static dfw_status batch_capture(dfw_batch* b, void* W, void* A, char* ws, int ns
   const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
   if (ie != hipSuccess) return fail(DFW_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
   b->execs.push_back(exec);
+  return DFW_OK;
+}
+
+// The rollout on `st`, and the copy of the control blocks to h (ngrids of them).  Does not wait for the last
+// chunks, on an error neither.
+static dfw_status batch_rollout(dfw_batch* b, void* W, void* A, char* ws, int nsteps, bool use_graph, double* dth,
+                                Ctrl* h, hipStream_t st) {
+  const bool chunked = b->params.t_end > 0.0 && nsteps > kChunkSteps;
+  if (chunked) {
+    for (hipEvent_t& e : b->chunk_done)
+      if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    if (!b->running) HIP_TRY(hipHostMalloc((void**)&b->running, 2 * sizeof(int), hipHostMallocDefault));
+  }
+  const int chunk = chunked ? kChunkSteps : nsteps;
+  int done = 0;
+  for (int c = 0; c == 0 || done < nsteps; ++c) {
+    if (c >= 2) {  // the chunk before the one in flight
+      HIP_TRY(hipEventSynchronize(b->chunk_done[c & 1]));
+      if (!*(volatile int*)&b->running[c & 1]) break;
+    }
+    const int n1 = std::min(nsteps, done + chunk);
+    int* running = chunked ? b->running + (c & 1) : nullptr;
+    if (use_graph) {
+      if ((size_t)c == b->execs.size()) {
+        const dfw_status s = batch_capture(b, W, A, ws, nsteps, done, n1, dth, running);
+        if (s != DFW_OK) return s;
+      }
+      hipError_t ge = hipSuccess;
+      timed(DFW_K_GRAPH, st, [&] { ge = hipGraphLaunch(b->execs[c], st); });
+      HIP_TRY(ge);
+    } else {
+      batch_enqueue(b, W, A, ws, nsteps, done, n1, dth, running, st);
+    }
+    if (chunked) HIP_TRY(hipEventRecord(b->chunk_done[c & 1], st));
+    done = n1;
+  }
+  if (done < nsteps && dth)
+    hipLaunchKernelGGL(k_dt_rest, dim3(b->ngrids), dim3(256), 0, st, (const Ctrl*)(ws + b->ctrl_off), dth, nsteps, done);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipMemcpyAsync(h, ws + b->ctrl_off, b->ngrids * sizeof(Ctrl), hipMemcpyDeviceToHost, st));
   return DFW_OK;
 }
 
@@ -1619,45 +1659,13 @@ dfw_status dfw_batch_run(dfw_batch* b, void* W_flat, void* alpha_flat, int32_t n
       b->g_nsteps = nsteps;
     }
   }
-  const bool chunked = b->params.t_end > 0.0 && nsteps > kChunkSteps;
-  if (chunked && !b->running) {
-    HIP_TRY(hipEventCreateWithFlags(&b->chunk_done[0], hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&b->chunk_done[1], hipEventDisableTiming));
-    HIP_TRY(hipHostMalloc((void**)&b->running, 2 * sizeof(int), hipHostMallocDefault));
-  }
-  const int chunk = chunked ? kChunkSteps : nsteps;
-  int done = 0;
-  for (int c = 0; c == 0 || done < nsteps; ++c) {
-    if (c >= 2) {  // the chunk before the one in flight
-      HIP_TRY(hipEventSynchronize(b->chunk_done[c & 1]));
-      if (!*(volatile int*)&b->running[c & 1]) break;
-    }
-    const int n1 = std::min(nsteps, done + chunk);
-    int* running = chunked ? b->running + (c & 1) : nullptr;
-    if (use_graph) {
-      if ((size_t)c == b->execs.size()) {
-        const dfw_status cs = batch_capture(b, W_flat, alpha_flat, (char*)ws, nsteps, done, n1, dt_hist_dev, running);
-        if (cs != DFW_OK) {
-          (void)hipStreamSynchronize(st);  // chunks before this one may be running
-          drop_graph(b);
-          return cs;
-        }
-      }
-      hipError_t ge = hipSuccess;
-      timed(DFW_K_GRAPH, st, [&] { ge = hipGraphLaunch(b->execs[c], st); });
-      HIP_TRY(ge);
-    } else {
-      batch_enqueue(b, W_flat, alpha_flat, (char*)ws, nsteps, done, n1, dt_hist_dev, running, st);
-    }
-    if (chunked) HIP_TRY(hipEventRecord(b->chunk_done[c & 1], st));
-    done = n1;
-  }
-  if (done < nsteps && dt_hist_dev)
-    hipLaunchKernelGGL(k_dt_rest, dim3(b->ngrids), dim3(256), 0, st, (const Ctrl*)((char*)ws + b->ctrl_off), dt_hist_dev,
-                       nsteps, done);
-  HIP_TRY(hipGetLastError());
   std::vector<Ctrl> h(b->ngrids);
-  HIP_TRY(hipMemcpyAsync(h.data(), (char*)ws + b->ctrl_off, b->ngrids * sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+  const dfw_status s = batch_rollout(b, W_flat, alpha_flat, (char*)ws, nsteps, use_graph != 0, dt_hist_dev, h.data(), st);
+  if (s != DFW_OK) {  // chunks before the failing call may still be running on the caller's buffers
+    (void)hipStreamSynchronize(st);
+    drop_graph(b);
+    return s;
+  }
   HIP_TRY(hipStreamSynchronize(st));
   int nbad = 0;
   for (int g = 0; g < b->ngrids; ++g) {
