@@ -15,18 +15,41 @@
 namespace dfw {
 namespace cand {
 
-// The IEEE results of 1/x and sqrt(x) in FP32 by the hardware's estimates and fused corrections, without the
-// range scaling of the general sequences (4 and 8 instructions instead of about 11 and 15).  Compared with the
-// compiler's division and root for all 2^32 arguments: 1/x is the same for every x of magnitude in
-// [2^-126, 2^126), zero, infinite and NaN, sqrt(x) for every x >= 2^-102, zero, infinite, negative and NaN;
-// outside they stay within a unit in the last place or flush a subnormal result.  They stand where they leave
-// the rest of the kernel's rounding alone: which product of a sum the compiler fuses depends on the code
-// around it, and with the DF's divisions or the GKS flux's shortened too the results moved in the last bit.
-// 4096^2 LF, 3 steps 15.8 -> 15.3 ms.
+// The IEEE results of 1/x and sqrt(x) in FP32 for every argument (tests/test_gpu_device_math.py compares all
+// 2^32 with the compiler's division and root), by the hardware's estimates and fused corrections: 4 instructions
+// and a branch, and 12, instead of about 11 and 15.  The corrections give the IEEE bits while all they form are
+// normal numbers.  For the root that is x from 2^-102 on; smaller ones are scaled by 2^64.  For 1/x it is where
+// that is a normal number itself; a wave with another operand takes the general division for all its lanes.
+// The branch around that division is written inside one asm statement: as control flow it would cut the code
+// around it into blocks, and which products of a sum the compiler fuses, and so the last bit of the results,
+// follows the blocks.  The two stand where they leave the rest of the kernel's rounding alone: with the DF's
+// divisions or the GKS flux's shortened too the results moved in the last bit.
+// 4096^2 LF, three steps, 15.7 -> 14.8 ms with both; GKS, which has most of its divisions elsewhere, 1 %.
 DFW_HD float recip(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm("" : "+v"(x));  // counts as one use of x, as a division by it does
-  return __builtin_amdgcn_div_fixupf(rcp_pos(x), x, 1.0f);
+  float r = rcp_pos(x), a, n, q, t;
+  constexpr int kNotNormal = 0x3ff & ~(1 << 3 | 1 << 8);  // class bits: all but the normal numbers
+  asm("v_cmp_class_f32 vcc, %0, %6\n\t"
+      "s_cbranch_vccz .Lrecip%=\n\t"
+      // 1 and x scaled into range, the quotient refined twice and scaled back, special cases
+      "v_div_scale_f32 %1, vcc, %5, %5, 1.0\n\t"
+      "v_div_scale_f32 %2, vcc, 1.0, %5, 1.0\n\t"
+      "v_rcp_f32 %0, %1\n\t"
+      "s_nop 1\n\t"
+      "v_fma_f32 %3, -%1, %0, 1.0\n\t"
+      "v_fma_f32 %0, %3, %0, %0\n\t"
+      "v_mul_f32 %3, %2, %0\n\t"
+      "v_fma_f32 %4, -%1, %3, %2\n\t"
+      "v_fma_f32 %3, %4, %0, %3\n\t"
+      "v_fma_f32 %4, -%1, %3, %2\n\t"
+      "v_div_fmas_f32 %0, %4, %0, %3\n\t"
+      "v_div_fixup_f32 %0, %0, %5, 1.0\n"
+      ".Lrecip%=:"
+      : "+&v"(r), "=&v"(a), "=&v"(n), "=&v"(q), "=&v"(t)
+      : "v"(x), "s"(kNotNormal)
+      : "vcc");
+  return r;
 #else
   return 1.0f / x;
 #endif
@@ -35,8 +58,10 @@ DFW_HD float recip(float x) {
 DFW_HD float root(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int kZeroOrInf = 1 << 5 | 1 << 6 | 1 << 9;  // class bits: -0, +0, +inf
-  const float y = __builtin_amdgcn_rsqf(x), s = x * y;
-  return __builtin_amdgcn_classf(x, kZeroOrInf) ? x : fmaf(fmaf(-s, s, x), 0.5f * y, s);
+  const bool small = x < 0x1p-102f;
+  const float t = __builtin_ldexpf(x, small ? 64 : 0), y = __builtin_amdgcn_rsqf(t), s = t * y;
+  const float r = __builtin_ldexpf(fmaf(fmaf(-s, s, t), 0.5f * y, s), small ? -32 : 0);
+  return __builtin_amdgcn_classf(x, kZeroOrInf) ? x : r;
 #else
   return sqrtf(x);
 #endif
