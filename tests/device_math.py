@@ -24,4 +24,6 @@ def load():
         f = getattr(L, name)
         f.restype = ctypes.c_int
         f.argtypes = [ctypes.c_void_p] * n + ([ctypes.c_int] if n > 1 else [])
+    L.dm_quotient.restype = ctypes.c_int
+    L.dm_quotient.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_double, ctypes.c_int]
     return L

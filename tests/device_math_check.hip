@@ -15,6 +15,11 @@ __global__ void k_f64(const double* x, double* rcp, double* s, double* is, int n
   dfw::sqrt_inv(x[i], s[i], is[i]);
 }
 
+__global__ void k_quotient(const double* x, double* q, double n, int count) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < count) q[i] = dfw::quotient_any(n, x[i]);
+}
+
 __global__ void k_f32(const float* x, float* rcp, float* root, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -45,6 +50,13 @@ __global__ void k_all(unsigned long long* bad) {
 extern "C" int dm_f64(const double* x, double* rcp, double* s, double* is, int n) {
   if (n < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_f64, dim3((n + 255) / 256), dim3(256), 0, nullptr, x, rcp, s, is, n);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : hipDeviceSynchronize();
+}
+
+extern "C" int dm_quotient(const double* x, double* q, double n, int count) {
+  if (count < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_quotient, dim3((count + 255) / 256), dim3(256), 0, nullptr, x, q, n, count);
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : hipDeviceSynchronize();
 }

@@ -5,6 +5,9 @@ rounded by one fused operation, so 1/x and the root lie within one unit in the l
 reciprocal, refined from the same estimate (its own final rounding, then the root's), within two; zero,
 infinite, NaN and negative operands give the IEEE results, which the failing states of a run rely on.
 
+FP64 quotient of a positive number (``quotient_any``): corrected by its residual, so within one unit too, and
+exactly 1 for n / n; the same special operands.
+
 FP32 (``cand::recip``, ``cand::root``): bit for bit the IEEE results for every argument, among them those
 whose reciprocal or root the estimates alone miss (1/x subnormal or overflowing, roots of numbers below
 2^-102, subnormal and negative subnormal ones)."""
@@ -72,6 +75,21 @@ def test_f64_ends_of_the_range():
     assert np.array_equal(r[~fin], want[0][~fin])
     assert _ulps(r[fin], want[0][fin]) <= 1
     assert _ulps(s, want[1]) <= 1 and _ulps(i, want[2]) <= 2
+
+
+@pytest.mark.parametrize("n", [1.0, 1.2**2, 1.4**2, (5.0 / 3.0) ** 2, 4.0])
+def test_f64_quotient(n):
+    x = np.concatenate([_arguments(np.float64), [n], SPECIAL])
+    d = torch.from_numpy(x).cuda()
+    q = torch.empty_like(d)
+    torch.cuda.synchronize()
+    assert device_math.load().dm_quotient(d.data_ptr(), q.data_ptr(), n, d.numel()) == 0
+    q = q.cpu().numpy()
+    k = len(x) - len(SPECIAL)
+    assert q[k - 1] == 1.0
+    assert _ulps(q[:k], n / x[:k]) <= 1
+    with np.errstate(all="ignore"):
+        assert np.array_equal(q[k:], n / x[k:], equal_nan=True)
 
 
 def test_f32_special_operands():
