@@ -204,11 +204,15 @@ constexpr int kFaceArgs = 6 * 8 + (int)sizeof(GridDesc) + 2 * 8 + (int)sizeof(Sc
 // In FP64 held to three waves per SIMD (168 registers): the GKS second stage needs more left to itself and
 // then runs two (4096^2, two steps: 17.8 -> 17.3 ms; 512^2 1.2 % faster).  It takes 167 without spills, with
 // the time limiter 168 and 12 bytes of scratch; the LF kernels take 136 to 158.  GKS in FP32 is held to
-// five waves (96 registers; 97 to 105 left to itself, four waves: 1001x750 1.70 -> 1.68 ms for four steps).
-constexpr int faces_waves(size_t element, int flux) { return element == 8 ? 3 : (flux == DFW_FLUX_GKS ? 5 : 1); }
+// five waves (96 registers and 8 to 44 bytes of scratch; 97 to 104 registers left to itself, four waves:
+// 1001x750 1.70 -> 1.68 ms for four steps), but not with the time limiter (98 to 105 registers; held to five
+// it spills 48 bytes: 700x800 345 -> 339 us per step, 58x78 39.6 -> 40.7).
+constexpr int faces_waves(size_t element, int flux, int out) {
+  return element == 8 ? 3 : (flux == DFW_FLUX_GKS && !(out & OUT_OMEGA) ? 5 : 1);
+}
 
 template <class real, int FLUX, int OUT, int TF, int TR>
-__global__ __launch_bounds__(TF * (TR + 4), faces_waves(sizeof(real), FLUX)) void k_faces(const real* __restrict__ Wall,
+__global__ __launch_bounds__(TF * (TR + 4), faces_waves(sizeof(real), FLUX, OUT)) void k_faces(const real* __restrict__ Wall,
                                                          const real* __restrict__ Aall,
                                                          real* __restrict__ FXall, real* __restrict__ FYall,
                                                          Ctrl* __restrict__ ctrls, GridDesc G0,
