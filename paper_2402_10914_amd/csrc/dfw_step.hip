@@ -65,9 +65,10 @@ __device__ __forceinline__ double bank_max(const Ctrl* ctrl, int bank) {
 // Reads one word of every 64-byte line of a kernel's first BYTES of arguments, all at once.  The
 // arguments are otherwise loaded where they are first used, one round trip after another in a kernel
 // whose blocks follow each other; after this they come from the scalar cache.  Launches of few
-// workgroups are bound by such chains: 20 steps of a 64 x 64 LF grid in FP64 870 -> 848 us, 512^2
-// GKS 0.8 % faster, 4096^2 GKS the same.  The FP32 interface kernel goes without: its five waves per
-// SIMD hide the chain, and 4096^2 LF ran 1.5 % slower with it.
+// workgroups are bound by such chains: us per step in FP64, without and with, 64 x 64 LF 31.9 / 30.5, GKS
+// 37.2 / 36.2, 100 x 100 LF 32.2 / 31.3, 512^2 LF 130.5 / 128.8, GKS 168.5 / 167.1; 4096^2 GKS the same.  The FP32
+// interface kernel goes without: its five waves per SIMD hide the chain, and 4096^2 LF ran 1.5 % slower
+// with it.
 template <int BYTES>
 __device__ __forceinline__ void touch_arguments() {
   const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
